@@ -2115,7 +2115,7 @@ int kgdb_candidate_logits(kgdb_batch* b, int32_t melt, uint64_t* keys, float* lo
   HIPCHK(hipMallocAsync((void**)&d_l, sizeof(float) * nk, b->s));
   HIPCHK(hipMemcpyAsync(d_k, keys, sizeof(uint64_t) * nk, hipMemcpyHostToDevice, b->s));
   launch_db_features(db_args(b), melt, d_k, (int)nk, d_f, b->s);
-  launch_mlp_forward(b->d_net, d_f, nk, d_l, nullptr, b->s);
+  launch_mlp_forward(b->d_net, d_f, nk, d_l, b->s);
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(logits, d_l, sizeof(float) * nk, hipMemcpyDeviceToHost, b->s));
   HIPCHK(hipFreeAsync(d_k, b->s));
@@ -2146,7 +2146,7 @@ int kgdb_mlp_forward(const float* params, const float* feat, int64_t n, float* l
   hipStream_t s = (hipStream_t)stream;
   MlpWork w = mlp_work_layout(ws, n);
   launch_mlp_quant(params, w.net, s);
-  launch_mlp_forward(w.net, feat, n, logit, nullptr, s);
+  launch_mlp_forward(w.net, feat, n, logit, s);
   HIPCHK(hipGetLastError());
   return 0;
 }
@@ -2158,20 +2158,24 @@ int kgdb_mlp_grad(const float* params, const float* feat, const int32_t* label, 
   hipStream_t s = (hipStream_t)stream;
   MlpWork w = mlp_work_layout(ws, n);
   launch_mlp_quant(params, w.net, s);
-  launch_mlp_forward(w.net, feat, n, w.logit, &w, s);
-  launch_mlp_grad(w, label, n, s);
-  if (grad) HIPCHK(hipMemcpyAsync(grad, w.grad, sizeof(double) * NN_NPARAM, hipMemcpyDeviceToDevice, s));
-  if (loss) HIPCHK(hipMemcpyAsync(loss, w.loss, sizeof(double), hipMemcpyDeviceToDevice, s));
+  launch_mlp_grad(w, feat, label, n, grad ? grad : w.grad, loss ? loss : w.loss, s);
   HIPCHK(hipGetLastError());
+  return 0;
+}
+
+static int adam_check(int64_t t, double lr, double b1, double b2, double eps, double* c1, double* c2) {
+  if (t < 1 || !(lr > 0) || !(b1 >= 0 && b1 < 1) || !(b2 >= 0 && b2 < 1) || !(eps > 0))
+    return fail(KGDB_E_PARAM, "need t >= 1, lr > 0, 0 <= b1, b2 < 1, eps > 0");
+  *c1 = 1.0 - std::pow(b1, (double)t);
+  *c2 = 1.0 - std::pow(b2, (double)t);
   return 0;
 }
 
 int kgdb_mlp_adam(float* params, float* m, float* v, const double* grad, int64_t t, double lr, double b1, double b2,
                   double eps, void* stream) {
   if (!params || !m || !v || !grad) return fail(KGDB_E_PARAM, "null argument");
-  if (t < 1 || !(lr > 0) || !(b1 >= 0 && b1 < 1) || !(b2 >= 0 && b2 < 1) || !(eps > 0))
-    return fail(KGDB_E_PARAM, "need t >= 1, lr > 0, 0 <= b1, b2 < 1, eps > 0");
-  const double c1 = 1.0 - std::pow(b1, (double)t), c2 = 1.0 - std::pow(b2, (double)t);
+  double c1, c2;
+  CHK(adam_check(t, lr, b1, b2, eps, &c1, &c2));
   launch_mlp_adam(params, m, v, grad, c1, c2, lr, b1, b2, eps, (hipStream_t)stream);
   HIPCHK(hipGetLastError());
   return 0;
@@ -2180,10 +2184,16 @@ int kgdb_mlp_adam(float* params, float* m, float* v, const double* grad, int64_t
 int kgdb_mlp_train_step(float* params, float* m, float* v, const float* feat, const int32_t* label, int64_t n,
                         int64_t t, double lr, double b1, double b2, double eps, void* ws, int64_t ws_bytes,
                         double* loss, void* stream) {
-  if (!params || !m || !v) return fail(KGDB_E_PARAM, "null argument");
-  CHK(kgdb_mlp_grad(params, feat, label, n, nullptr, loss, ws, ws_bytes, stream));
+  if (!params || !m || !v || !feat || !label) return fail(KGDB_E_PARAM, "null argument");
+  CHK(mlp_check_ws(n, ws, ws_bytes));
+  double c1, c2;
+  CHK(adam_check(t, lr, b1, b2, eps, &c1, &c2));
+  hipStream_t s = (hipStream_t)stream;
   MlpWork w = mlp_work_layout(ws, n);
-  return kgdb_mlp_adam(params, m, v, w.grad, t, lr, b1, b2, eps, stream);
+  launch_mlp_quant(params, w.net, s);
+  launch_mlp_step(w, feat, label, n, params, m, v, c1, c2, lr, b1, b2, eps, loss ? loss : w.loss, s);
+  HIPCHK(hipGetLastError());
+  return 0;
 }
 }  // extern "C"
 
@@ -2195,7 +2205,7 @@ int kgdb_mlp_train_step(float* params, float* m, float* v, const float* feat, co
 // overlap); every kernel of the step writes the parts it reads, so nothing needs clearing.
 // ---------------------------------------------------------------------------------------
 namespace {
-constexpr size_t STATIC_WS_BYTES = nn_work_bytes(KGDB_MLP_STATIC_ROWS, 256);
+constexpr size_t STATIC_WS_BYTES = nn_work_bytes(KGDB_MLP_STATIC_ROWS);
 constexpr int MAX_DEVICES = 64;
 }  // namespace
 

@@ -1268,7 +1268,7 @@ __device__ void score_keys(const MeltDesc& d, const Topo& T, const DbArgs& a, co
         nn_zero_input(t, threadIdx.x);
       }
     }
-    nn_forward_tile<DB_BLOCK / 64>(t, a.net, nullptr);
+    nn_forward_tile<DB_BLOCK / 64>(t, a.net);
     if (threadIdx.x < NN_TILE && r0 + (int)threadIdx.x < n) w[r0 + threadIdx.x] = nn_weight(t.logit[threadIdx.x]);
   }
   __syncthreads();
@@ -1458,7 +1458,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_learned(DbArgs a) {
     }
     // the reverse weights of the round's attempts: one 16-row pass of the tile (the rows of
     // attempts without an allowed reverse move are not used)
-    nn_forward_tile<LS_WAVES, 1>(s_t, a.net, nullptr);  // synchronises
+    nn_forward_tile<LS_WAVES, 1>(s_t, a.net);  // synchronises
     if (att + wv < K && lane == 0) {
       LearnedEval& ev = s_ev[wv];
       const double wr = ev.rev ? nn_weight(s_t.logit[wv]) : 0.0;

@@ -7,6 +7,7 @@ namespace kgdb {
 
 struct MeltDesc;
 struct NetQ;
+struct NetRecord;
 
 // lanes that cooperate on one cell in the cell finalisation (blocks of 256 threads); the
 // fused force kernel is built for 1, 2, 4 or 8 lanes per monomer (chosen at run time)
@@ -211,24 +212,23 @@ void launch_db_features(const DbArgs& a, int melt, const uint64_t* keys, int nke
 // ---- network of the learned proposal (kgdb_mlp.hip)
 struct MlpWork {  // training workspace carved from one device buffer
   NetQ* net;
-  int16_t* xq;
-  uint8_t* code;
-  uint8_t* mask;
-  float* logit;
-  double* gs;
-  double* g;
-  double* lossp;
-  double* part;
+  NetRecord* rec;  // rows' records for the backward pass
+  double* gs;      // output deltas
+  double* lossp;   // sums of row losses
+  double* part;    // partial gradients
   double* grad;
   double* loss;
-  int nchunk;
   size_t bytes;
 };
 MlpWork mlp_work_layout(void* base, int64_t n);  // base == nullptr: sizes only
 void launch_mlp_quant(const float* P, NetQ* q, hipStream_t s);
-void launch_mlp_forward(const NetQ* net, const float* feat, int64_t n, float* logit, const MlpWork* rec,
-                        hipStream_t s);
-void launch_mlp_grad(const MlpWork& w, const int32_t* label, int64_t n, hipStream_t s);
+void launch_mlp_forward(const NetQ* net, const float* feat, int64_t n, float* logit, hipStream_t s);
+// gradient and mean loss of n rows; or one Adam step on them
+void launch_mlp_grad(const MlpWork& w, const float* feat, const int32_t* label, int64_t n, double* grad, double* loss,
+                     hipStream_t s);
+void launch_mlp_step(const MlpWork& w, const float* feat, const int32_t* label, int64_t n, float* P, float* m,
+                     float* v, double c1, double c2, double lr, double b1, double b2, double eps, double* loss,
+                     hipStream_t s);
 void launch_mlp_adam(float* P, float* m, float* v, const double* g, double c1, double c2, double lr, double b1,
                      double b2, double eps, hipStream_t s);
 size_t netq_bytes();

@@ -35,6 +35,7 @@ constexpr int NN_SA0 = NN_INP + 8;        // LDS row strides (bf16), padded agai
 constexpr int NN_SA = NN_H + 8;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // quantised network in device memory (weights as bf16 code/64; row o holds unit o's inputs)
@@ -48,17 +49,38 @@ struct alignas(256) NetQ {
   float pad_[3];
 };
 
+// A training step of n rows runs in up to nn_parts_cap(n) workgroups, each of which leaves a
+// partial gradient (292 KB) that the reduction reads back.  Up to 8192 rows at most 128 of them:
+// 16 rows take a workgroup about 8 us, and every further partial costs the reduction.
+// Beyond that one per CU.  The cap grows with n, so a workspace for n rows serves fewer rows too.
+constexpr int NN_ROWBLOCK = 16;  // rows of one MFMA row block
+constexpr int nn_parts_cap(int64_t n) {
+  return n > 8192 ? 256 : (n + NN_ROWBLOCK - 1) / NN_ROWBLOCK < 128 ? (int)((n + NN_ROWBLOCK - 1) / NN_ROWBLOCK) : 128;
+}
+// rows per workgroup (whole row blocks)
+constexpr int64_t nn_part_rows(int64_t n) {
+  const int64_t cap = nn_parts_cap(n) > 0 ? nn_parts_cap(n) : 1;
+  return ((n + cap - 1) / cap + NN_ROWBLOCK - 1) / NN_ROWBLOCK * NN_ROWBLOCK;
+}
+
+// What a training forward pass leaves of 16 rows, by column: the input codes / 64 and the hidden
+// codes / 16 as bf16, the sign bit of a hidden one (they are never negative) set where the unit
+// passes gradient.
+struct alignas(16) NetRecord {
+  uint16_t x[NN_INP][NN_ROWBLOCK];
+  uint16_t h[3][NN_H][NN_ROWBLOCK];
+};
+
 // Bytes of the training workspace for n rows, laid out as mlp_work_layout carves it (every
-// piece rounded up to 256 bytes): the quantised network, per-row input codes, hidden codes and
-// masks, logits, FP64 deltas and losses, per-chunk partial gradients, the gradient and the
-// loss.  chunk = rows per partial weight-gradient sum.
+// piece rounded up to 256 bytes): the quantised network, the rows' records and output deltas, the
+// losses of the forward workgroups (at most one per row block), the partial gradients, the
+// gradient and the loss.  Records are kept for whole 64-row tiles.
 constexpr size_t nn_align256(size_t x) { return (x + 255) & ~(size_t)255; }
-constexpr size_t nn_work_bytes(int64_t n, int chunk) {
-  return nn_align256(sizeof(NetQ)) + nn_align256(sizeof(int16_t) * NN_INP * (size_t)n) +
-         2 * nn_align256(3 * NN_H * (size_t)n) + nn_align256(sizeof(float) * (size_t)n) +
-         nn_align256(sizeof(double) * (size_t)n) + nn_align256(sizeof(double) * 3 * NN_H * (size_t)n) +
-         nn_align256(sizeof(double) * (size_t)n) +
-         nn_align256(sizeof(double) * NN_NPARAM * (size_t)((n + chunk - 1) / chunk > 0 ? (n + chunk - 1) / chunk : 1)) +
+constexpr size_t nn_blocks(int64_t n) { return (size_t)((n + NN_TILE - 1) / NN_TILE * (NN_TILE / NN_ROWBLOCK)); }
+constexpr size_t nn_work_bytes(int64_t n) {
+  return nn_align256(sizeof(NetQ)) + nn_align256(sizeof(NetRecord) * nn_blocks(n)) +
+         nn_align256(sizeof(double) * NN_ROWBLOCK * nn_blocks(n)) + nn_align256(sizeof(double) * nn_blocks(n)) +
+         nn_align256(sizeof(double) * NN_NPARAM * (size_t)(nn_parts_cap(n) > 0 ? nn_parts_cap(n) : 1)) +
          nn_align256(sizeof(double) * NN_NPARAM) + nn_align256(sizeof(double));
 }
 
@@ -70,17 +92,11 @@ struct alignas(16) NetTile {
   float logit[NN_TILE];
 };
 
-__device__ __forceinline__ int nn_clamp255(double r, int lo) {
-  if (r > 255.0) return 255;
-  if (r < (double)lo) return lo;
-  return (int)r;
-}
-__device__ __forceinline__ int q_weight(float w) { return nn_clamp255(rint((double)w * 64.0), -255); }
-__device__ __forceinline__ int q_input(float f) { return nn_clamp255(rint((double)f * 64.0), -255); }
-__device__ __forceinline__ int q_hidden(float z) {
-  if (!(z > 0.0f)) return 0;
-  return nn_clamp255((double)rintf(z * 16.0f), 0);
-}
+// (in FP32: scaling by a power of two and rounding to an integer are exact there)
+__device__ __forceinline__ float nn_clamp255(float r, float lo) { return r > 255.0f ? 255.0f : r < lo ? lo : r; }
+__device__ __forceinline__ int q_weight(float w) { return (int)nn_clamp255(rintf(w * 64.0f), -255.0f); }
+__device__ __forceinline__ int q_input(float f) { return (int)nn_clamp255(rintf(f * 64.0f), -255.0f); }
+__device__ __forceinline__ float q_hidden(float z) { return z > 0.0f ? nn_clamp255(rintf(z * 16.0f), 0.0f) : 0.0f; }
 // a hidden unit passes gradient when it is neither cut by the ReLU nor saturated
 __device__ __forceinline__ bool nn_in_range(float z) { return z > 0.0f && z < NN_HMAX; }
 
@@ -107,34 +123,39 @@ __device__ __forceinline__ void nn_zero_input(NetTile& t, int r) {
   for (int k = 0; k < NN_INP; ++k) t.a0[r][k] = (__bf16)0.0f;
 }
 
-// Optional per-row record of a training forward pass: input codes, hidden codes and the
-// in-range mask of every hidden unit (rows >= nrow are not written).
-struct NetRecord {
-  int16_t* xq;    // [row][NN_INP]
-  uint8_t* code;  // [row][3][NN_H]
-  uint8_t* mask;  // [row][3][NN_H]
-  int nrow;
-};
-
 // One hidden layer over the first 16 RB rows of a tile: RB x 8 output blocks of 16 x 16 on
 // v_mfma_f32_16x16x32_bf16.  Wavefront wv of NW owns the output column blocks wv, wv + NW, ...:
 // the weight fragments of a column block are loaded once and serve all of its row blocks.
 // Operand layout of the instruction (wave64): lane l supplies row l%16 of A and column l%16 of
 // B, each with the 8 consecutive k of block l/16; it receives rows 4(l/16)..4(l/16)+3 of column
-// l%16 of the result.
-template <int K, int NW, int RB>
+// l%16 of the result.  With a record, the codes are also written by column for the backward pass.
+// A layer's weight fragments are loaded apart from their use, so that a caller can request them ahead.
+template <int K, int NW>
+struct NnFrag {
+  static constexpr int CT = 8 / NW;
+  bf16x8 w[CT][K / 32];
+  float b[CT];
+  __device__ __forceinline__ void load(const __bf16* __restrict__ W, const float* __restrict__ bias) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const int col = (wv + c * NW) * 16 + (lane & 15);
+#pragma unroll
+      for (int kk = 0; kk < K / 32; ++kk) w[c][kk] = *(const bf16x8*)(W + col * K + (lane >> 4) * 8 + kk * 32);
+      b[c] = bias[col];
+    }
+  }
+};
+template <int K, int NW, int RB, int LAYER = -1>
 __device__ __forceinline__ void nn_layer(const __bf16* __restrict__ in, int in_stride, __bf16* __restrict__ out,
-                                         const __bf16* __restrict__ W, const float* __restrict__ bias,
-                                         const NetRecord* rec, int layer) {
+                                         const NnFrag<K, NW>& f, NetRecord* __restrict__ rec = nullptr) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r16 = lane & 15, kq = lane >> 4;
-  for (int ct = wv; ct < 8; ct += NW) {
-    bf16x8 bw[K / 32];
-    const __bf16* bp = W + (ct * 16 + r16) * K + kq * 8;
 #pragma unroll
-    for (int kk = 0; kk < K / 32; ++kk) bw[kk] = *(const bf16x8*)(bp + kk * 32);
-    const int col = ct * 16 + r16;
-    const float bb = bias[col];
+  for (int c = 0; c < NnFrag<K, NW>::CT; ++c) {
+    const int col = (wv + c * NW) * 16 + r16;
+    const bf16x8* bw = f.w[c];
+    const float bb = f.b[c];
 #pragma unroll
     for (int rt = 0; rt < RB; ++rt) {
       f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -142,47 +163,54 @@ __device__ __forceinline__ void nn_layer(const __bf16* __restrict__ in, int in_s
 #pragma unroll
       for (int kk = 0; kk < K / 32; ++kk)
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8*)(ap + kk * 32), bw[kk], acc, 0, 0, 0);
+      u16x4 c4;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int row = rt * 16 + kq * 4 + i;
         const float z = acc[i] + bb;
-        const int c = q_hidden(z);
-        out[row * NN_SA + col] = (__bf16)((float)c * 0.0625f);
-        if (rec && row < rec->nrow) {
-          const size_t o = ((size_t)row * 3 + layer) * NN_H + col;
-          rec->code[o] = (uint8_t)c;
-          rec->mask[o] = nn_in_range(z) ? 1 : 0;
-        }
+        const __bf16 h = (__bf16)(q_hidden(z) * 0.0625f);
+        out[row * NN_SA + col] = h;
+        if constexpr (LAYER >= 0) c4[i] = (uint16_t)(__builtin_bit_cast(uint16_t, h) | (nn_in_range(z) ? 0x8000u : 0u));
       }
+      if constexpr (LAYER >= 0) *(u16x4*)&rec[rt].h[LAYER][col][kq * 4] = c4;
     }
   }
+}
+
+// Logits of the first 16 RB rows of the last hidden layer's codes a into logit.  The products
+// (c/16)(c'/64) and all their partial sums are exact in FP32, so the TPR lanes of a row may split
+// its 128 products and add their partial sums in any order.
+template <int NW, int RB>
+__device__ __forceinline__ void nn_output(const __bf16 (*a)[NN_SA], const NetQ* __restrict__ net, float* logit) {
+  constexpr int TPR0 = (NW * 64) / (16 * RB), TPR = TPR0 < 64 ? TPR0 : 64;
+  static_assert(TPR >= 1 && (TPR & (TPR - 1)) == 0, "lanes per output row");
+  const int r = threadIdx.x / TPR, j = threadIdx.x % TPR;
+  float s = 0.0f;
+#pragma unroll
+  for (int k = j * (NN_H / TPR); k < (j + 1) * (NN_H / TPR); ++k) s += (float)a[r][k] * net->w4[k];
+#pragma unroll
+  for (int o = TPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (j == 0) logit[r] = s + net->b4;
 }
 
 // Logits of the first 16 RB rows of the tile (inputs already in t.a0) into t.logit; the other
 // rows are left alone (each output row depends on its own input row only).  Block-cooperative:
 // every thread of the workgroup (NW wavefronts) must call it.
 template <int NW, int RB = 4>
-__device__ void nn_forward_tile(NetTile& t, const NetQ* __restrict__ net, const NetRecord* rec) {
+__device__ void nn_forward_tile(NetTile& t, const NetQ* __restrict__ net) {
   __syncthreads();
-  nn_layer<NN_INP, NW, RB>(&t.a0[0][0], NN_SA0, &t.a1[0][0], &net->W1[0][0], net->b1, rec, 0);
+  NnFrag<NN_INP, NW> f1;
+  f1.load(&net->W1[0][0], net->b1);
+  nn_layer<NN_INP, NW, RB>(&t.a0[0][0], NN_SA0, &t.a1[0][0], f1);
   __syncthreads();
-  nn_layer<NN_H, NW, RB>(&t.a1[0][0], NN_SA, &t.a2[0][0], &net->W2[0][0], net->b2, rec, 1);
+  NnFrag<NN_H, NW> f2;
+  f2.load(&net->W2[0][0], net->b2);
+  nn_layer<NN_H, NW, RB>(&t.a1[0][0], NN_SA, &t.a2[0][0], f2);
   __syncthreads();
-  nn_layer<NN_H, NW, RB>(&t.a2[0][0], NN_SA, &t.a1[0][0], &net->W3[0][0], net->b3, rec, 2);
+  f2.load(&net->W3[0][0], net->b3);
+  nn_layer<NN_H, NW, RB>(&t.a2[0][0], NN_SA, &t.a1[0][0], f2);
   __syncthreads();
-  // output unit: products (c/16)(c'/64) and all their partial sums are exact in FP32, so the
-  // TPR lanes of a row may split its 128 products and add their partial sums in any order
-  constexpr int TPR = (NW * 64) / (16 * RB);
-  static_assert(TPR >= 1 && TPR <= 64 && (TPR & (TPR - 1)) == 0, "lanes per output row");
-  {
-    const int r = threadIdx.x / TPR, j = threadIdx.x % TPR;
-    float s = 0.0f;
-#pragma unroll
-    for (int k = j * (NN_H / TPR); k < (j + 1) * (NN_H / TPR); ++k) s += (float)t.a1[r][k] * net->w4[k];
-#pragma unroll
-    for (int o = TPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (j == 0) t.logit[r] = s + net->b4;
-  }
+  nn_output<NW, RB>(t.a1, net, t.logit);
   __syncthreads();
 }
 
