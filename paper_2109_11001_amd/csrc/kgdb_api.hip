@@ -133,6 +133,7 @@ struct kgdb_batch {
   uint64_t* d_step = nullptr;
   uint32_t* d_err = nullptr;
   double* d_out4 = nullptr;
+  double4* d_epart = nullptr;      // energy sums of blocks of 256 monomers
   int *d_cnt13 = nullptr, *d_bucket13 = nullptr, *d_nnb = nullptr, *d_nbr = nullptr, *d_ncand = nullptr;
   uint64_t *d_cand = nullptr, *d_sweep = nullptr, *d_probe_keys = nullptr;
   int cand_cap = DB_CAND_CAP;      // candidate keys per melt
@@ -1002,7 +1003,7 @@ static double fit_ellK(const std::vector<double>& r2n, int N, double l0) {
 static int melt_observables(kgdb_batch* b, int32_t melt, double* r2_over_n, double* ell_K, double* mean_bond) {
   const MeltDesc& d = b->D[melt];
   launch_prefix(b->d_md, melt, d.M, b->NP, b->d_x[b->cur], b->d_chain, b->d_spre, b->d_blen, b->s);
-  launch_r2(b->d_md, melt, d.M, d.N, b->d_spre, nullptr, b->d_r2, b->s);
+  launch_r2(d.M, d.N, b->d_spre, b->d_r2, b->s);
   HIPCHK(hipGetLastError());
   std::vector<double> r2(std::max(d.N - 1, 1)), bl(d.M);
   HIPCHK(hipMemcpyAsync(r2.data(), b->d_r2, sizeof(double) * (d.N - 1), hipMemcpyDeviceToHost, b->s));
@@ -1217,6 +1218,11 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
   step(dalloc(b, &b->d_step, (size_t)count));
   step(dalloc(b, &b->d_err, (size_t)count));
   step(dalloc(b, &b->d_out4, 4 * (size_t)count));
+  {
+    size_t nblk = 0;
+    for (const MeltDesc& d : b->D) nblk += (size_t)(d.Nm + 255) / 256;
+    step(dalloc(b, &b->d_epart, nblk));
+  }
   step(dalloc(b, &b->d_cnt13, (size_t)NC13));
   step(dalloc(b, &b->d_bucket13, (size_t)NC13 * DB_CELL_CAP));
   step(dalloc(b, &b->d_nnb, np));
@@ -1482,7 +1488,7 @@ int kgdb_forces(kgdb_batch* b, int32_t melt, double* F, double* S, double* E3) {
   ForceArgs a = force_args(b);
   a.fc = b->d_diagF;
   launch_force(b->prec, F_DIAG, b->lanes, a, force_blocks(b), b->s);
-  launch_reduce_melt(b->d_md, b->nm, b->NP, b->d_E, b->d_v, b->d_out4, b->s);
+  launch_reduce_melt(b->d_md, b->nm, b->pm, b->NP, b->d_E, b->d_v, b->d_epart, b->d_out4, b->s);
   HIPCHK(hipGetLastError());
   CHK(check_errors(b));
   const MeltDesc& d = b->D[melt];
@@ -1508,7 +1514,7 @@ int kgdb_energy(kgdb_batch* b, int32_t melt, double out[4]) {
   ForceArgs a = force_args(b);
   a.fc = b->d_diagF;
   launch_force(0, F_DIAG | F_EXACT, b->lanes, a, force_blocks(b), b->s);  // FP64 from the master positions
-  launch_reduce_melt(b->d_md, b->nm, b->NP, b->d_E, b->d_v, b->d_out4, b->s);
+  launch_reduce_melt(b->d_md, b->nm, b->pm, b->NP, b->d_E, b->d_v, b->d_epart, b->d_out4, b->s);
   HIPCHK(hipGetLastError());
   CHK(check_errors(b));
   HIPCHK(hipMemcpy(out, b->d_out4 + 4 * melt, 4 * sizeof(double), hipMemcpyDeviceToHost));
@@ -1744,8 +1750,8 @@ int kgdb_pair_correlation(kgdb_batch* b, int32_t melt, double r_max, int32_t nbi
   unsigned long long* dh = nullptr;
   HIPCHK(hipMallocAsync((void**)&dh, sizeof(unsigned long long) * nbins, b->s));
   launch_fill_i32((int*)dh, 2 * nbins, 0, b->s);
-  launch_pair_hist(b->d_md, melt, d.Nm, b->NP, b->d_x[b->cur], b->d_cell_of, b->d_cnt[b->cur], b->d_bucket, r_max,
-                   nbins, R, dh, b->s);
+  launch_pair_hist(b->d_md, melt, d.nc, b->NP, b->d_x[b->cur], b->d_cnt[b->cur], b->d_bucket, r_max, nbins, R, dh,
+                   b->s);
   std::vector<unsigned long long> h(nbins);
   const hipError_t e1 = hipGetLastError();
   const hipError_t e2 = hipMemcpyAsync(h.data(), dh, sizeof(unsigned long long) * nbins, hipMemcpyDeviceToHost, b->s);
@@ -1772,13 +1778,17 @@ int kgdb_structure_factor(kgdb_batch* b, int32_t melt, const int32_t* nvec, int6
   int* dn = nullptr;
   double* dS = nullptr;
   HIPCHK(hipMallocAsync((void**)&dn, sizeof(int) * 3 * nq, b->s));
+  const MeltDesc& d = b->D[melt];
+  double2* dp = nullptr;
   HIPCHK(hipMallocAsync((void**)&dS, sizeof(double) * nq, b->s));
+  HIPCHK(hipMallocAsync((void**)&dp, sizeof(double2) * nq * structure_runs(d.Nm, nq), b->s));
   HIPCHK(hipMemcpyAsync(dn, nvec, sizeof(int) * 3 * nq, hipMemcpyHostToDevice, b->s));
-  launch_structure_factor(b->d_md, melt, b->NP, b->d_x[b->cur], dn, nq, dS, b->s);
+  launch_structure_factor(b->d_md, melt, d.Nm, b->NP, b->d_x[b->cur], dn, nq, dp, dS, b->s);
   const hipError_t e1 = hipGetLastError();
   const hipError_t e2 = hipMemcpyAsync(S, dS, sizeof(double) * nq, hipMemcpyDeviceToHost, b->s);
   (void)hipFreeAsync(dn, b->s);
   (void)hipFreeAsync(dS, b->s);
+  (void)hipFreeAsync(dp, b->s);
   HIPCHK(hipStreamSynchronize(b->s));
   if (e1 != hipSuccess || e2 != hipSuccess) return fail(KGDB_E_HIP, "structure factor");
   return 0;

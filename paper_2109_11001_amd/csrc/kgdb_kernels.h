@@ -149,22 +149,23 @@ void launch_random_walks(const MeltDesc* md, int nm, int max_M, int NP, double* 
                          hipStream_t s);
 void launch_fr_chains(const MeltDesc* md, int nm, int max_M, int NP, double* x, const int* tries, hipStream_t s);
 double kuhn_over_l0(double kappa);  // Eq. 12
-void launch_pair_hist(const MeltDesc* md, int k, int Nm, int NP, const double* x, const int* cell_of,
-                      const int* cnt, const int* bucket, double r_max, int nbins, int R, unsigned long long* hist,
-                      hipStream_t s);
-void launch_structure_factor(const MeltDesc* md, int k, int NP, const double* x, const int* nvec, int64_t nq,
-                             double* S, hipStream_t s);
+void launch_pair_hist(const MeltDesc* md, int k, int nc, int NP, const double* x, const int* cnt, const int* bucket,
+                      double r_max, int nbins, int R, unsigned long long* hist, hipStream_t s);
+// S(q) of nq vectors; part holds structure_runs(Nm, nq) x nq partial sums
+int structure_runs(int Nm, int64_t nq);
+void launch_structure_factor(const MeltDesc* md, int k, int Nm, int NP, const double* x, const int* nvec, int64_t nq,
+                             double2* part, double* S, hipStream_t s);
 void launch_msd_track(const MeltDesc* md, const BlockMap& pm, int NP, const double* x, const int* mono, double* last,
                       double* acc, int reset, int only, hipStream_t s);
 void launch_msd_reduce(const MeltDesc* md, int k, int NP, const double* acc, double* out, hipStream_t s);
 void launch_velocities(const MeltDesc* md, const BlockMap& pm, int NP, double* v, hipStream_t s);
 void launch_remove_mean(const MeltDesc* md, int nm, int NP, double* v, hipStream_t s);
-void launch_reduce_melt(const MeltDesc* md, int nm, int NP, const double* outE, const double* v,
-                        double* out4, hipStream_t s);
+// part: one double4 per block of pm
+void launch_reduce_melt(const MeltDesc* md, int nm, const BlockMap& pm, int NP, const double* outE, const double* v,
+                        double4* part, double* out4, hipStream_t s);
 void launch_prefix(const MeltDesc* md, int k, int M, int NP, const double* x, const int* chain, double* spre,
                    double* blen, hipStream_t s);
-void launch_r2(const MeltDesc* md, int k, int M, int N, const double* spre, double* part, double* r2sum,
-               hipStream_t s);
+void launch_r2(int M, int N, const double* spre, double* r2sum, hipStream_t s);
 
 // ---- double bridging (kgdb_db.hip)
 struct DbArgs {

@@ -1,0 +1,73 @@
+"""The readings' kernels at the edges of their splits: pair histograms whose staged cells reach round
+the box, whose staged batch is too dense to fit at once, or whose bins fill the LDS histogram; S(q)
+of one vector and of a remainder of 64; chains at the edges of the 256-bond pass; energies of melts
+that end inside a block of 256 monomers."""
+import numpy as np
+import pytest
+
+from oracle import oracle as o
+from tests import inputs
+
+pytestmark = pytest.mark.gpu
+
+kg = pytest.importorskip("paper_2109_11001_amd")
+torch = pytest.importorskip("torch")
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+
+def pair(**kw):
+    om = o.Melt(**kw)
+    gm = kg.Melt(**dict(kw, warmup_steps=0))
+    st = om.get_state()
+    gm.set_state(0, x=st["x"], v=st["v"], fl=st["fl"], chains=st["chains"], counters=st["counters"])
+    return om, gm
+
+
+@pytest.mark.parametrize("kw,r_max,nbins", [
+    (dict(M=4, N=14, seed=3), 1.3, 40),      # 3 cells a side: every cell staged once
+    (dict(M=20, N=50, seed=4), 4.6, 8192),   # halo of 4 cells in a box of 9; all of the LDS bins
+    (dict(M=60, N=50, seed=5), 3.0, 150),    # 13 cells a side: a last tile of one cell
+    (dict(M=60, N=50, seed=6), 0.05, 3),
+])
+def test_pair_histogram_edges(kw, r_max, nbins):
+    om, gm = pair(warmup_steps=0, **kw)
+    counts, _ = gm.pair_correlation(r_max, nbins)
+    assert np.array_equal(counts, om.pair_hist(r_max, nbins))
+
+
+def test_pair_histogram_of_a_dense_half():
+    # all monomers in half of the box along each axis but one: a staged batch of 1024 cells holds
+    # more than the LDS takes at once
+    kw = dict(M=60, N=100, seed=7, warmup_steps=0)
+    om, gm = pair(**kw)
+    x = inputs.random_positions(6000, om.L, 7)
+    x[:2] *= 0.5
+    om.set_state(x=x)
+    gm.set_state(0, x=x)
+    counts, _ = gm.pair_correlation(4.0, 64)
+    assert np.array_equal(counts, om.pair_hist(4.0, 64))
+
+
+@pytest.mark.parametrize("nq", [1, 63, 65])
+def test_structure_factor_of_few_vectors(nq):
+    om, gm = pair(M=7, N=33, seed=8, warmup_steps=50)
+    nv = np.random.default_rng(nq).integers(-20, 21, size=(nq, 3))
+    nv[0] = (0, 0, 0)  # S(0) = N_m exactly
+    Sg, So = gm.structure_factor(nv), om.structure_factor(nv)
+    assert Sg[0] == pytest.approx(231.0, rel=1e-15)
+    # sums of 231 unit phasors: phases of up to 60 turns rounded to 2^-53 of themselves on either side
+    assert np.all(np.abs(Sg - So) <= 1e-12 * 231 * (1 + np.sqrt(So)))
+
+
+@pytest.mark.parametrize("kw", [dict(M=60, N=4), dict(M=5, N=256), dict(M=5, N=257), dict(M=3, N=258), dict(M=2, N=700)])
+def test_observables_and_energy_edges(kw):
+    om, gm = pair(seed=9, kappa=1.5, warmup_steps=50, **kw)
+    M, N = kw["M"], kw["N"]
+    r2g, _, bg = gm.observables()
+    r2o, _, bo = om.observables()
+    terms = M * (N - np.arange(1, N))
+    assert np.all(np.abs(r2g - r2o) <= 2 * terms * 2.0 ** -53 * r2o + 1e-300)
+    assert bg == pytest.approx(bo, rel=M * N * 2.0 ** -52)
+    assert np.allclose(gm.energy(), om.energy(), rtol=1e-12, atol=0)
