@@ -251,6 +251,43 @@ __device__ void move_features(const MeltDesc& d, const Topo& T, const double* __
   f[24] = (float)d.kappa;
 }
 
+// Bead b (0-7) of the learned proposal's inputs for move mv in topology T (see move_features).
+__device__ __forceinline__ int feature_bead(const Topo& T, const Move& mv, int N, int b) {
+  if (b < 4) {
+    int p = mv.i - 1 + b;
+    p = p < 1 ? 1 : (p > N ? N : p);
+    return T.at(mv.A, p);
+  }
+  int q = mv.var == 0 ? mv.j + 2 - (b - 4) : mv.j - 1 + (b - 4);
+  q = q < 1 ? 1 : (q > N ? N : q);
+  return T.at(mv.B, q);
+}
+
+// Inputs 0-23 of move mv in topology T by a wavefront, with move_features' arithmetic (lane b < 8 takes
+// bead b).
+__device__ __forceinline__ void move_features_wave(const MeltDesc& d, const Topo& T, const double* __restrict__ x,
+                                                   int NP, const Move& mv, float* f) {
+  const int id = feature_bead(T, mv, d.N, threadIdx.x & 7);
+  double dd[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) dd[c] = x[(size_t)c * NP + id];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) dd[c] = min_image(dd[c] - __shfl(dd[c], 1, 64), d.L);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const double cen = ((__shfl(dd[c], 2, 64) + __shfl(dd[c], 5, 64)) + __shfl(dd[c], 6, 64)) * 0.25;
+    if ((threadIdx.x & 63) < 8) f[3 * (threadIdx.x & 7) + c] = (float)(dd[c] - cen);
+  }
+}
+// their record of a training log
+__device__ __forceinline__ void log_record(const DbArgs& a, int k, const MeltDesc& d, int64_t rec, const float* f,
+                                           int accepted) {
+  const int lane = threadIdx.x & 63;
+  const size_t r = (size_t)k * a.log_cap + rec;
+  if (lane < NN_IN) a.log_feat[r * NN_IN + lane] = lane < 24 ? f[lane] : (float)d.kappa;
+  if (lane == 0) a.log_label[r] = accepted;
+}
+
 // full candidate list: each monomer u on the lower chain of a close pair
 __global__ __launch_bounds__(256) void k_db_cands(const MeltDesc* __restrict__ md, const int* __restrict__ blk_melt,
                                                   const int* __restrict__ blk_base, DbArgs a) {
@@ -598,6 +635,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
   __shared__ uint8_t s_nrev[DB_NEW_CAP];
   __shared__ int s_dst[DB_NEW_CAP];             // their places in the merged list
   __shared__ AttemptEval s_ev[DB_WAVES];
+  __shared__ float s_feat[DB_WAVES][24];  // training log: inputs of the round's moves
   __shared__ uint64_t s_rw[DB_BLOCK];           // draws of attempts c0 .. c0 + DB_BLOCK - 1: choice word,
   __shared__ double s_ru[DB_BLOCK];             // and acceptance uniform
   __shared__ int s_tmp[DB_BLOCK / 64];
@@ -605,7 +643,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
   __shared__ int s_total, s_nrm;
   __shared__ uint32_t s_err;
   __shared__ int s_accept;
-  __shared__ int64_t s_logn, s_logat;  // training log: records written, record of this attempt
 
   const int k = blockIdx.x;
   const MeltDesc& d = a.md[k];
@@ -617,7 +654,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
   __shared__ double sum_dE;
   if (threadIdx.x == 0) {
     s_err = 0;
-    s_logn = 0;
     n_att = n_nocand = n_acc = n_norev = sum_nc = 0;
     sum_dE = 0.0;
   }
@@ -665,7 +701,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
   const uint64_t kstride = (uint64_t)(N - 1) * (uint64_t)M * (uint64_t)(N - 1) * 2u;  // key span of one first chain
   const double T = d.T;
   const int literal = d.proposal == KGDB_PROPOSAL_LITERAL;
-  int64_t att = 0, c0 = -(int64_t)DB_BLOCK;
+  int64_t att = 0, c0 = -(int64_t)DB_BLOCK, logn = 0;  // logn: records written
   while (att < K) {
     // the draws depend on the attempt index only: one thread per attempt, a chunk at a time
     if (att + DB_WAVES > c0 + DB_BLOCK) {
@@ -688,6 +724,8 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
       const int ci = (int)(att - c0) + wv;
       const int idx = (int)rng_choice(s_rw[ci], (uint64_t)n);
       const Move mv = decode_key(s_keys[idx], d);
+      // training record: inputs of the proposed move in the topology it is proposed in
+      if (a.log_feat) move_features_wave(d, Topo{a.chain, a.loc, d.off, N, {mv.A, mv.i, mv.B, mv.j, -1}}, a.x, a.NP, mv, s_feat[wv]);
       // keys with chain pair (A, B) lie among the keys whose first chain is A
       const int lo = wave_lower_bound(s_keys, n, (uint64_t)mv.A * kstride, lane);
       const int hi = wave_lower_bound(s_keys, n, (uint64_t)(mv.A + 1) * kstride, lane);
@@ -713,7 +751,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
     __syncthreads();
     // ---- walk the evaluated attempts in order
     const int nev = (int)min((int64_t)DB_WAVES, K - att);
-    int used = nev;
+    int used = nev, accepted = 0;
     for (int w = 0; w < nev; ++w) {
       const Move mv = s_ev[w].mv;
       const int phase = s_ev[w].phase, old_ab = s_ev[w].old_ab;
@@ -731,17 +769,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
         n_att++;
         sum_nc += n;
         if (!literal && !s_ev[w].rev) n_norev++;
-        // training record: inputs of the proposed move in the topology it was proposed in
-        s_logat = -1;
-        if (a.log_feat && s_logn < a.log_cap) {
-          s_logat = s_logn++;
-          const Topo To{a.chain, a.loc, d.off, N, {mv.A, mv.i, mv.B, mv.j, -1}};
-          float f[NN_IN];
-          move_features(d, To, a.x, a.NP, mv, f);
-          const size_t r = (size_t)k * a.log_cap + s_logat;
-          for (int q = 0; q < NN_IN; ++q) a.log_feat[r * NN_IN + q] = f[q];
-          a.log_label[r] = 0;
-        }
       }
       if (phase == 0) continue;
       touching_after(d, a, mv, s_keys, s_pair, n, s_cnt, s_new, &s_err, DB_NEW_CAP);
@@ -764,7 +791,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
                         (old_ab <= DB_CAND_CAP - DB_NEW_CAP);
         if ((u < ratio) && !acc) s_err |= ERR_CAND_OVERFLOW;
         if (acc) { n_acc++; sum_dE += dE; }
-        if (acc && s_logat >= 0) a.log_label[(size_t)k * a.log_cap + s_logat] = 1;
         s_accept = acc;
         s_nrm = 0;
       }
@@ -867,7 +893,12 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
         __syncthreads();
       }
       used = w + 1;  // attempts after an accepted one are evaluated again
+      accepted = 1;
       break;
+    }
+    if (a.log_feat) {  // each wavefront its attempt's record
+      if (wv < used && logn + wv < a.log_cap) log_record(a, k, d, logn + wv, s_feat[wv], accepted && wv == used - 1);
+      logn = min(logn + used, a.log_cap);
     }
     att += used;
     __syncthreads();  // s_ev and s_cnt are rewritten by the next round
@@ -883,7 +914,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep(DbArgs a) {
     st->ncand_end = n;
     if (s_err) atomicOr(&a.err[k], s_err);
     a.ncand[k] = n;
-    if (a.log_n) a.log_n[k] = s_logn;
+    if (a.log_n) a.log_n[k] = logn;
   }
   for (int t = threadIdx.x; t < n; t += blockDim.x) a.cand[(size_t)k * a.cand_cap + t] = s_keys[t];
 }
@@ -905,6 +936,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
   __shared__ uint8_t s_nrev[DB_NEW_CAP];
   __shared__ int s_dst[DB_NEW_CAP];
   __shared__ AttemptEval s_ev[DB_WAVES];
+  __shared__ float s_feat[DB_WAVES][24];  // training log: inputs of the round's moves
   __shared__ uint64_t s_rw[DB_BLOCK];
   __shared__ double s_ru[DB_BLOCK];
   __shared__ int s_tmp[DB_BLOCK / 64];
@@ -912,7 +944,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
   __shared__ int s_total, s_nrm;
   __shared__ uint32_t s_err;
   __shared__ int s_accept;
-  __shared__ int64_t s_logn, s_logat;
   __shared__ int64_t n_att, n_nocand, n_acc, n_norev, sum_nc;
   __shared__ double sum_dE;
 
@@ -926,7 +957,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
   kgdb_db_stats* st = (kgdb_db_stats*)a.stats + k;
   if (threadIdx.x == 0) {
     s_err = 0;
-    s_logn = 0;
     n_att = n_nocand = n_acc = n_norev = sum_nc = 0;
     sum_dE = 0.0;
   }
@@ -971,7 +1001,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
   const uint64_t kstride = (uint64_t)(N - 1) * (uint64_t)M * (uint64_t)(N - 1) * 2u;
   const double T = d.T;
   const int literal = d.proposal == KGDB_PROPOSAL_LITERAL;
-  int64_t att = 0, c0 = -(int64_t)DB_BLOCK;
+  int64_t att = 0, c0 = -(int64_t)DB_BLOCK, logn = 0;  // logn: records written
   while (att < K) {
     if (att + DB_WAVES > c0 + DB_BLOCK) {
       c0 = att;
@@ -993,6 +1023,8 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
       const int ci = (int)(att - c0) + wv;
       const int idx = (int)rng_choice(s_rw[ci], (uint64_t)n);
       const Move mv = decode_key(keys[idx], d);
+      // training record: inputs of the proposed move in the topology it is proposed in
+      if (a.log_feat) move_features_wave(d, Topo{a.chain, a.loc, d.off, N, {mv.A, mv.i, mv.B, mv.j, -1}}, a.x, a.NP, mv, s_feat[wv]);
       const int lo = wave_lower_bound(keys, n, (uint64_t)mv.A * kstride, lane);
       const int hi = wave_lower_bound(keys, n, (uint64_t)(mv.A + 1) * kstride, lane);
       const uint32_t want = ((uint32_t)mv.A << 16) | (uint32_t)mv.B;
@@ -1014,7 +1046,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
     __syncthreads();
     // ---- walk the evaluated attempts in order
     const int nev = (int)min((int64_t)DB_WAVES, K - att);
-    int used = nev;
+    int used = nev, accepted = 0;
     for (int w = 0; w < nev; ++w) {
       const Move mv = s_ev[w].mv;
       const int phase = s_ev[w].phase, old_ab = s_ev[w].old_ab;
@@ -1032,16 +1064,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
         n_att++;
         sum_nc += n;
         if (!literal && !s_ev[w].rev) n_norev++;
-        s_logat = -1;
-        if (a.log_feat && s_logn < a.log_cap) {
-          s_logat = s_logn++;
-          const Topo To{a.chain, a.loc, d.off, N, {mv.A, mv.i, mv.B, mv.j, -1}};
-          float f[NN_IN];
-          move_features(d, To, a.x, a.NP, mv, f);
-          const size_t r = (size_t)k * a.log_cap + s_logat;
-          for (int q = 0; q < NN_IN; ++q) a.log_feat[r * NN_IN + q] = f[q];
-          a.log_label[r] = 0;
-        }
       }
       if (phase == 0) continue;
       touching_after(d, a, mv, keys, pair, n, s_cnt, s_new, &s_err, DB_NEW_CAP);
@@ -1062,7 +1084,6 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
         const int acc = (u < ratio) && (s_cnt[1] <= DB_NEW_CAP) && (n_new <= cap) && (old_ab <= DB_NEW_CAP);
         if ((u < ratio) && !acc) s_err |= ERR_CAND_OVERFLOW;
         if (acc) { n_acc++; sum_dE += dE; }
-        if (acc && s_logat >= 0) a.log_label[(size_t)k * a.log_cap + s_logat] = 1;
         s_accept = acc;
         s_nrm = 0;
       }
@@ -1144,7 +1165,12 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
         __syncthreads();
       }
       used = w + 1;
+      accepted = 1;
       break;
+    }
+    if (a.log_feat) {  // each wavefront its attempt's record
+      if (wv < used && logn + wv < a.log_cap) log_record(a, k, d, logn + wv, s_feat[wv], accepted && wv == used - 1);
+      logn = min(logn + used, a.log_cap);
     }
     att += used;
     __syncthreads();
@@ -1160,7 +1186,7 @@ __global__ __launch_bounds__(DB_BLOCK) void k_db_sweep_big(DbArgs a) {
     st->ncand_end = n;
     if (s_err) atomicOr(&a.err[k], s_err);
     a.ncand[k] = n;
-    if (a.log_n) a.log_n[k] = s_logn;
+    if (a.log_n) a.log_n[k] = logn;
   }
   for (int t = threadIdx.x; t < n; t += blockDim.x) a.cand[(size_t)k * cap + t] = keys[t];
 }
@@ -1272,18 +1298,6 @@ __device__ void score_keys(const MeltDesc& d, const Topo& T, const DbArgs& a, co
     if (threadIdx.x < NN_TILE && r0 + (int)threadIdx.x < n) w[r0 + threadIdx.x] = nn_weight(t.logit[threadIdx.x]);
   }
   __syncthreads();
-}
-
-// Bead b (0-7) of the learned proposal's inputs for move mv in topology T (see move_features).
-__device__ __forceinline__ int feature_bead(const Topo& T, const Move& mv, int N, int b) {
-  if (b < 4) {
-    int p = mv.i - 1 + b;
-    p = p < 1 ? 1 : (p > N ? N : p);
-    return T.at(mv.A, p);
-  }
-  int q = mv.var == 0 ? mv.j + 2 - (b - 4) : mv.j - 1 + (b - 4);
-  q = q < 1 ? 1 : (q > N ? N : q);
-  return T.at(mv.B, q);
 }
 
 // Inputs from the positions of the eight beads held by lanes 0-7 of a wavefront (lane b: bead
