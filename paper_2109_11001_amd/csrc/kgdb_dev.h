@@ -176,7 +176,13 @@ __device__ __forceinline__ double wrap_box(double x, double L) {
   if (w >= L) w = 0.0;
   return w;
 }
-__device__ __forceinline__ double min_image(double d, double L) { return d - L * rint(d / L); }
+// nearest image of a difference of two wrapped coordinates, |d| < L: d - L rint(d / L) without the
+// division.  (The comparison decides as the rounded quotient does: at |d| = L / 2 both keep d, and the
+// next larger |d| divides to more than 1/2.)
+__device__ __forceinline__ double min_image(double d, double L) {
+  const double h = 0.5 * L;
+  return d > h ? d - L : (d < -h ? d + L : d);
+}
 // wrap_box for a coordinate that has left [0, L) by less than one box: the same result
 // (x + L and x - L round as x - L floor(x / L) does there), without the division.  (A step
 // moves a monomer far less than a box; a coordinate beyond that, of a run already flagged as
