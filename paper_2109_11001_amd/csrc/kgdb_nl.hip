@@ -288,10 +288,10 @@ __device__ __forceinline__ int find_cell(const int* s, int lo, int hi, int v) {
 constexpr int NLB_CELLS = 594;  // staged cells: 3 (nl_S + 2)(nl_Sy + 2) <= 594
 // batches of at most this many list tiles find a tile's first slot inside the rebuild kernel
 constexpr int TILE_SUM_MAX = 4096;
-constexpr int STAGE_PER_THREAD = (STAGE_CAP_MAX + NLB_THREADS - 1) / NLB_THREADS;
-
-// a staged member: position relative to the tile frame, and (rebuild only) its old slot
-template <typename R> struct alignas(16) Staged { R x, y, z; int tag; };
+// bucket entries of a staged cell that its thread requests before it knows the cell's count; a cell
+// with more (rare: a cell of the longest interval holds about five) is ranked by a wavefront instead
+constexpr int RB_PF = 12;
+constexpr int RB_PAD = 8;  // staged entries past the capacity (a row is tested four members at a time)
 
 // 16-byte word q (eight 16-bit entries) of the list of the monomer in slot i
 __device__ __forceinline__ size_t nl_word(int i, int q) {
@@ -313,28 +313,42 @@ __device__ __forceinline__ int member_slot(const NlArgs& a, int sc, int n, int r
   return b[0];
 }
 
+// Staged positions of a rebuild decide list membership only.  They are kept in 16 bits an axis (x in
+// the low, y in the high half of the first word, z in the second), U units a cell edge, U <= 10922, so
+// that members up to two cells apart differ by less than 2^15 and their squared distance fits an int:
+// five integer instructions test a candidate.  Each is rounded to half a unit, so two members' distance
+// is off by at most sqrt(3) units; the cutoff is taken two units further out, and the few entries that
+// this adds lie outside every cutoff of the step and contribute nothing.
+typedef short i16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ int quant_test(uint2 p, uint2 me, int minus_r2) {  // < 0: within the cutoff
+  const i16x2 xy = __builtin_bit_cast(i16x2, p.x) - __builtin_bit_cast(i16x2, me.x);
+  const i16x2 z = __builtin_bit_cast(i16x2, p.y) - __builtin_bit_cast(i16x2, me.y);
+  return __builtin_amdgcn_sdot2(xy, xy, __builtin_amdgcn_sdot2(z, z, minus_r2, false), false);
+}
+
 // The list of one home monomer (staged position me, staged index tme, home cell (ih, yy) of
 // the frame): staged members within r_list in the 3 x 3 rows of three cells around it.  A
-// row, or a side cell of it, whose nearest point is beyond r_list plus a margin (far above the
-// rounding of frame coordinates) holds no member within r_list and is skipped.  at(t) gives
-// staged member t.  Each entry is stored as it is found (16 bits; entry j of slot g lies in
-// word nl_word(g, j / 8) at place j % 8), so that taking a candidate costs no branch.  The last
-// word is filled up with `pad`, the index one past the stage, where the step keeps a position
-// outside every cutoff: the step reads whole words without testing the list's end.
-template <typename R, typename At>
-__device__ __forceinline__ int nl_list_one(const NlArgs& a, int g, const Staged<R>& me, int tme, int ih, int yy,
-                                           int W, int WY, R hl, R rl2, R rskip2, const int* s_off, int pad, At at) {
+// row, or a side cell of it, whose nearest point is beyond r_list plus a margin holds no member
+// within r_list and is skipped.  at(t) gives staged member t (read up to three past a row's end).
+//
+// A row's candidates are tested into a bit mask, then its set bits are stored: the test is then free
+// of the bookkeeping of an entry (28 instructions a candidate when each was stored as it was found,
+// 7 now; a list takes a seventh of its candidates).  Entry j of slot g lies in word nl_word(g, j / 8)
+// at place j % 8.  The last word is filled up with `pad`, the index one past the stage, where the
+// step keeps a position outside every cutoff: the step reads whole words without testing the list's end.
+template <typename At>
+__device__ __forceinline__ int nl_list_one(const NlArgs& a, int g, uint2 me, int tme, int ih, int yy, int W, int WY,
+                                           float U, int minus_r2, float rskip2, const int* s_off, int pad, At at) {
   uint16_t* __restrict__ out = (uint16_t*)a.nlist + nl_word(g, 0) * 8;
   int cnt = 0;
-  const R cx0 = (R)(ih - 1) * hl, cy0 = (R)(yy - 1) * hl;
-  const R dxl = me.x - cx0, dxr = cx0 + hl - me.x;
-  const R dyl = me.y - cy0, dyr = cy0 + hl - me.y;
-  const R dzl = me.z, dzr = hl - me.z;
+  const float dxl = (float)(me.x & 0xffffu) - (float)ih * U, dxr = U - dxl;
+  const float dyl = (float)(me.x >> 16) - (float)yy * U, dyr = U - dyl;
+  const float dzl = (float)me.y - U, dzr = U - dzl;
   for (int zz = 0; zz < 3; ++zz) {
-    const R ez = zz == 0 ? dzl : (zz == 2 ? dzr : (R)0);
+    const float ez = zz == 0 ? dzl : (zz == 2 ? dzr : 0.0f);
     for (int dy = -1; dy <= 1; ++dy) {
-      const R ey = dy < 0 ? dyl : (dy > 0 ? dyr : (R)0);
-      const R e2 = ey * ey + ez * ez;
+      const float ey = dy < 0 ? dyl : (dy > 0 ? dyr : 0.0f);
+      const float e2 = ey * ey + ez * ez;
       const int c0 = (zz * WY + yy + dy) * W + ih - 1;  // cells c0 .. c0 + 2: x offsets -1, 0, +1
       int b = s_off[c0], e = s_off[c0 + 3];
       if (e2 > rskip2) {
@@ -343,17 +357,27 @@ __device__ __forceinline__ int nl_list_one(const NlArgs& a, int g, const Staged<
         if (dxl * dxl + e2 > rskip2) b = s_off[c0 + 1];
         if (dxr * dxr + e2 > rskip2) e = s_off[c0 + 2];
       }
-      for (int t0 = b; t0 < e; t0 += 4) {
-        Staged<R> p[4];
+      for (int s0 = b; s0 < e; s0 += 32) {  // (a row holds about fifteen)
+        const int n = min(e - s0, 32);
+        uint32_t mask = 0;
+        int t = 0;
+        for (; t < n; t += 4) {
+          uint2 p[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) p[u] = at(min(t0 + u, e - 1));
+          for (int u = 0; u < 4; ++u) p[u] = at(s0 + t + u, e);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const R dx = p[u].x - me.x, dy2 = p[u].y - me.y, dz = p[u].z - me.z;
-          if (t0 + u < e && t0 + u != tme && dx * dx + dy2 * dy2 + dz * dz < rl2) {
-            if (cnt < NL_CAP) out[(cnt >> 3) * 512 + (cnt & 7)] = (uint16_t)(t0 + u);
-            ++cnt;
-          }
+          for (int u = 0; u < 4; ++u)  // shift the test's sign bit in
+            mask = __builtin_amdgcn_alignbit(mask, (uint32_t)quant_test(p[u], me, minus_r2), 31);
+        }
+        mask <<= 32 - t;                   // candidate s0 at bit 31
+        mask &= 0xffffffffu << (32 - n);   // none past the row
+        const uint32_t self = (uint32_t)(tme - s0);
+        if (self < 32u) mask &= ~(0x80000000u >> self);
+        while (mask) {
+          const int u = __builtin_clz(mask);
+          mask &= ~(0x80000000u >> u);
+          if (cnt < NL_CAP) out[(cnt >> 3) * 512 + (cnt & 7)] = (uint16_t)(s0 + u);
+          ++cnt;
         }
       }
     }
@@ -364,140 +388,163 @@ __device__ __forceinline__ int nl_list_one(const NlArgs& a, int g, const Staged<
 
 template <typename R>
 __global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
-  // the stage holds FP32 frame positions in both precisions: they only decide list membership,
-  // whose cutoff carries a margin far above their rounding
   extern __shared__ __align__(16) unsigned char s_dyn[];
-  Staged<float>* s_pos = (Staged<float>*)s_dyn;
-  // monomer ids (then old slots and staged cells) of the staged members in binning order: they
-  // share the stage's memory and are consumed before it is written
-  int* s_mono = (int*)s_dyn;
+  uint2* const s_pos = (uint2*)s_dyn;                             // staged members, by cell and monomer id
+  int* const s_old = (int*)(s_pos + a.stage_cap + RB_PAD);        // their old slots
+  uint16_t* const s_hmap = (uint16_t*)(s_old + a.stage_cap + RB_PAD);  // home cell of each home: y << 8 | x of the frame
   __shared__ int s_off[NLB_CELLS + 1];
   __shared__ int s_sc[NLB_CELLS];
   __shared__ int s_home[NLB_CELLS + 1];  // prefix of the home cells' counts, sorted order
   __shared__ uint8_t s_wrap[NLB_CELLS];  // per staged cell and axis: periodic wrap -1, 0, +1 (2 bits each, +1)
+  __shared__ uint16_t s_big[NLB_CELLS];  // cells of more than RB_PF members
+  __shared__ int s_nbig;
   const int lb = xcd_remap(blockIdx.x, gridDim.x);
   const int k = __builtin_amdgcn_readfirstlane(a.rblk_melt[lb]);
   const int lt = a.rblk_base[lb];
   const MeltDesc& d = a.md[k];
   const TileGeo tg = tile_geo(d, lt);
   const int W = tg.nh + 2, WY = tg.nhy + 2, ncell = 3 * WY * W;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const double hl = d.hl;
   const int nc = d.ncl;
+  // units per cell edge, and per unit length
+  const int U = 65535 / max(max(W, WY), 6);
+  const double qs = (double)U / hl;
 
-  // the first PF bucket entries (ids and slots) of a thread's first staged cell are read with the
-  // cell's count, so that they arrive meanwhile (entries past the count are read and not used)
-  constexpr int PF = 8;
-  int pf_mono[PF], pf_slot[PF];
+  int id[RB_PF], slot[RB_PF];
+  auto fetch = [&](int sc) {
+    const int4* bm = (const int4*)(a.bucket_mono + (size_t)sc * NL_CELL_CAP);
+    const int4* br = (const int4*)(a.bucket_raw + (size_t)sc * NL_CELL_CAP);
+#pragma unroll
+    for (int q = 0; q < RB_PF / 4; ++q) {
+      const int4 m = bm[q], r = br[q];
+      id[4 * q] = m.x; id[4 * q + 1] = m.y; id[4 * q + 2] = m.z; id[4 * q + 3] = m.w;
+      slot[4 * q] = r.x; slot[4 * q + 1] = r.y; slot[4 * q + 2] = r.z; slot[4 * q + 3] = r.w;
+    }
+  };
   // the first slot of this tile: with few tiles in the batch, the sum of the counts of the tiles
   // before it, read here with the cells' counts (no scan kernel); else the scan's result
   const int tile = d.tile_off + lt;
   __shared__ int s_tsum[NLB_THREADS / 64];
   const bool tile_sum = a.ntile_total <= TILE_SUM_MAX;
+  const int nhc = tg.nh * tg.nhy;
+  if (threadIdx.x == 0) s_nbig = 0;
+  for (int t = threadIdx.x; t < ncell; t += NLB_THREADS) {
+    const StagedCell s = staged_cell(d, tg, W, WY, t);
+    const int sc = sorted_cell(d, s.ax, s.ay, s.az, nullptr);
+    const int n = min(a.cnt[sc], NL_CELL_CAP);
+    // (a thread's first cell: its members' ids and slots arrive with the count)
+    if (t == (int)threadIdx.x) fetch(sc);
+    s_sc[t] = sc;
+    s_off[t + 1] = n;
+    if (s.zz == 1 && s.yy >= 1 && s.yy <= tg.nhy && s.i >= 1 && s.i <= tg.nh)
+      s_home[(s.yy - 1) * tg.nh + s.i] = n;
+    const int wx = s.ax - (tg.x0 - 1 + s.i), wy = s.ay - (tg.y0 - 1 + s.yy), wz = s.az - (tg.cz - 1 + s.zz);
+    s_wrap[t] = (uint8_t)((wx > 0) - (wx < 0) + 1 + (((wy > 0) - (wy < 0) + 1) << 2) + (((wz > 0) - (wz < 0) + 1) << 4));
+  }
   if (tile_sum) {
     int part = 0;
     for (int t = threadIdx.x; t < tile; t += NLB_THREADS) part += a.tcnt[t];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) part += __shfl_xor(part, o, 64);
-    if ((threadIdx.x & 63) == 0) s_tsum[threadIdx.x >> 6] = part;
-  }
-  for (int t = threadIdx.x; t < ncell; t += NLB_THREADS) {
-    const StagedCell s = staged_cell(d, tg, W, WY, t);
-    const int sc = sorted_cell(d, s.ax, s.ay, s.az, nullptr);
-    s_sc[t] = sc;
-    s_off[t + 1] = min(a.cnt[sc], NL_CELL_CAP);
-    if (t == (int)threadIdx.x) {
-#pragma unroll
-      for (int j = 0; j < PF; ++j) {
-        pf_mono[j] = a.bucket_mono[(size_t)sc * NL_CELL_CAP + j];
-        pf_slot[j] = a.bucket_raw[(size_t)sc * NL_CELL_CAP + j];
-      }
-    }
-    const int wx = s.ax - (tg.x0 - 1 + s.i), wy = s.ay - (tg.y0 - 1 + s.yy), wz = s.az - (tg.cz - 1 + s.zz);
-    s_wrap[t] = (uint8_t)((wx > 0) - (wx < 0) + 1 + (((wy > 0) - (wy < 0) + 1) << 2) + (((wz > 0) - (wz < 0) + 1) << 4));
+    if (lane == 0) s_tsum[wv] = part;
   }
   __syncthreads();
-  if (threadIdx.x < 64) wave_prefix(s_off, ncell);
+  if (wv == 0) wave_prefix(s_off, ncell);
+  if (wv == 1) wave_prefix(s_home, nhc);
   __syncthreads();
-  const int total = s_off[ncell];
+  const int total = s_off[ncell], nhome = s_home[nhc];
   const bool staged = total <= a.stage_cap && !(d.test_flags & TF_NL_GLOBAL);
   if (threadIdx.x == 0 && !(d.test_flags & TF_NL_GLOBAL) && a.nlstat) {
     atomicMax(&a.nlstat[1], (uint32_t)total);
     if (!staged) atomicAdd(&a.nlstat[0], 1u);
   }
-  // staged member of cell t with rank r: its frame position (from the FP64 position relative
-  // to its grid cell, plus the staged cell's place in the frame) and its old slot
-  // (the frame's cell (i, yy, zz) is grid cell (x0 - 1 + i, y0 - 1 + yy, cz - 1 + zz) up to the
-  // recorded periodic wrap, so that the frame origin of a member is (x0, y0, cz) + wrap nc)
-  auto make = [&](int t, int slot) {
+  // staged member of cell t: its frame position (the frame's cell (i, yy, zz) is grid cell
+  // (x0 - 1 + i, y0 - 1 + yy, cz - 1 + zz) up to the recorded periodic wrap, so that the frame origin
+  // of a member is (x0 - 1, y0 - 1, cz - 1) + wrap nc), rounded to units
+  auto origin = [&](int t, double o[3]) {
     const int f = s_wrap[t];
-    Staged<float> m;
-    m.x = (float)(a.x[slot] - (double)(tg.x0 + ((f & 3) - 1) * nc) * hl);
-    m.y = (float)(a.x[a.NP + slot] - (double)(tg.y0 + (((f >> 2) & 3) - 1) * nc) * hl);
-    m.z = (float)(a.x[2 * a.NP + slot] - (double)(tg.cz + ((f >> 4) - 1) * nc) * hl);
-    m.tag = slot;
-    return m;
+    o[0] = 0.5 - (double)(tg.x0 - 1 + ((f & 3) - 1) * nc) * U;
+    o[1] = 0.5 - (double)(tg.y0 - 1 + (((f >> 2) & 3) - 1) * nc) * U;
+    o[2] = 0.5 - (double)(tg.cz - 1 + ((f >> 4) - 1) * nc) * U;
   };
+  auto quant = [&](double x, double y, double z, const double o[3]) {
+    const int qx = (int)__builtin_fma(x, qs, o[0]), qy = (int)__builtin_fma(y, qs, o[1]), qz = (int)__builtin_fma(z, qs, o[2]);
+    return make_uint2((uint32_t)min(max(qx, 0), 65535) | ((uint32_t)min(max(qy, 0), 65535) << 16),
+                      (uint32_t)min(max(qz, 0), 32767));
+  };
+  const int NP = a.NP;
   if (staged) {
-    // (1) the binned members' monomer ids (binned with them), old slots and staged cells, a
-    // staged cell per thread (three int arrays of `total` in the stage's memory, 12 of its 16
-    // bytes per member)
-    int* const s_slot = s_mono + total;
-    int* const s_cq = s_mono + 2 * total;
+    // a cell a thread: each member's rank by id gives its place in the stage
     for (int t = threadIdx.x; t < ncell; t += NLB_THREADS) {
       const int b0 = s_off[t], n = s_off[t + 1] - b0;
-      int j0 = 0;
-      if (t == (int)threadIdx.x) {
+      if (t != (int)threadIdx.x) fetch(s_sc[t]);
+      const int row = t / W, ih = t - row * W, zz = row / WY, yy = row - zz * WY;
+      if (zz == 1 && yy >= 1 && yy <= tg.nhy && ih >= 1 && ih <= tg.nh) {
+        const int h0 = s_home[(yy - 1) * tg.nh + ih - 1];
+        for (int j = 0; j < n; ++j) s_hmap[h0 + j] = (uint16_t)(yy << 8 | ih);
+      }
+      if (n > RB_PF) {
+        s_big[atomicAdd(&s_nbig, 1)] = (uint16_t)t;
+        continue;
+      }
+      int r[RB_PF];
 #pragma unroll
-        for (int j = 0; j < PF; ++j)
-          if (j < n) {
-            s_mono[b0 + j] = pf_mono[j];
-            s_slot[b0 + j] = pf_slot[j];
-            s_cq[b0 + j] = t;
+      for (int j = 0; j < RB_PF; ++j) {
+        id[j] = j < n ? id[j] : 0x7fffffff;
+        slot[j] = j < n ? slot[j] : d.off;
+        r[j] = b0;
+      }
+      auto rank = [&](int m) {  // among the first m
+#pragma unroll
+        for (int j = 0; j < RB_PF; ++j)
+#pragma unroll
+          for (int q = j + 1; q < RB_PF; ++q)
+            if (q < m) {
+              const int lt2 = id[j] < id[q];
+              r[q] += lt2;
+              r[j] += 1 - lt2;
+            }
+      };
+      if (__ballot(n > 8)) rank(RB_PF);
+      else rank(8);
+      double o[3];
+      origin(t, o);
+#pragma unroll
+      for (int q = 0; q < RB_PF / 4; ++q) {
+        if (!__ballot(n > 4 * q)) break;
+        double x[4], y[4], z[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          x[j] = a.x[slot[4 * q + j]];
+          y[j] = a.x[(size_t)NP + slot[4 * q + j]];
+          z[j] = a.x[2 * (size_t)NP + slot[4 * q + j]];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (4 * q + j < n) {
+            s_pos[r[4 * q + j]] = quant(x[j], y[j], z[j], o);
+            s_old[r[4 * q + j]] = slot[4 * q + j];
           }
-        j0 = PF;
-      }
-      const int* __restrict__ bm = a.bucket_mono + (size_t)s_sc[t] * NL_CELL_CAP;
-      const int* __restrict__ br = a.bucket_raw + (size_t)s_sc[t] * NL_CELL_CAP;
-#pragma unroll 4
-      for (int j = j0; j < n; ++j) {
-        s_mono[b0 + j] = bm[j];
-        s_slot[b0 + j] = br[j];
-        s_cq[b0 + j] = t;
       }
     }
     __syncthreads();
-    // (2) each member's rank by id within its cell gives its place in the stage (held in
-    // registers until every id has been read: cell q and place packed, and the old slot)
-    int pl[STAGE_PER_THREAD], sl[STAGE_PER_THREAD];
-#pragma unroll
-    for (int i = 0; i < STAGE_PER_THREAD; ++i) {
-      const int u = (int)threadIdx.x + i * NLB_THREADS;
-      pl[i] = -1;
-      sl[i] = 0;
-      if (u < total) {
-        const int q = s_cq[u];
-        const int b = s_off[q], e = s_off[q + 1], m = s_mono[u];
-        int r = 0;
-        for (int w = b; w < e; ++w) r += s_mono[w] < m;
-        pl[i] = ((b + r) << 10) | q;
-        sl[i] = s_slot[u];
+    const int nbig = s_nbig;
+    for (int q = wv; q < nbig; q += NLB_THREADS / 64) {  // a member a lane
+      const int t = s_big[q], b0 = s_off[t], n = s_off[t + 1] - b0;
+      const size_t e = (size_t)s_sc[t] * NL_CELL_CAP + min(lane, n - 1);
+      const int me = a.bucket_mono[e], sl = a.bucket_raw[e];
+      int r = 0;
+      for (int m = 0; m < n; ++m) r += __shfl(me, m, 64) < me;
+      double o[3];
+      origin(t, o);
+      if (lane < n) {
+        s_pos[b0 + r] = quant(a.x[sl], a.x[(size_t)NP + sl], a.x[2 * (size_t)NP + sl], o);
+        s_old[b0 + r] = sl;
       }
     }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < STAGE_PER_THREAD; ++i)
-      if (pl[i] >= 0) s_pos[pl[i] >> 10] = make(pl[i] & 1023, sl[i]);
+    if (nbig) __syncthreads();
   }
-  // home cells (frame z index 1, rows 1 .. nhy, x 1 .. nh) in sorted order: their counts
-  const int nhc = tg.nh * tg.nhy;
-  for (int c = threadIdx.x; c < nhc; c += NLB_THREADS) {
-    const int ly = c / tg.nh, lx = c - ly * tg.nh;
-    const int t = (WY + ly + 1) * W + lx + 1;
-    s_home[c + 1] = s_off[t + 1] - s_off[t];
-  }
-  __syncthreads();
-  if (threadIdx.x < 64) wave_prefix(s_home, nhc);
-  __syncthreads();
   int first = 0;
   if (tile_sum) {
 #pragma unroll
@@ -510,23 +557,33 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
     const int t = (WY + ly + 1) * W + lx + 1;
     a.cellsc[s_sc[t]] = make_int2(first + s_home[c], s_home[c + 1] - s_home[c]);
   }
-  const int nhome = s_home[nhc];
-  const float hlr = (float)hl;
-  const float rl2 = (float)(d.rlist2 * 1.0002);
-  const double rsk = sqrt(d.rlist2) + 1e-3;
-  const float rskip2 = (float)(rsk * rsk);
-  const int NP = a.NP;
+  const float rl = (float)(sqrt(d.rlist2 * 1.0002) * qs) + 2.0f, rsk = rl + 4.0f;
+  const int minus_r2 = -(int)(rl * rl) - 1;
+  const float rskip2 = rsk * rsk;
   for (int h = threadIdx.x; h < nhome; h += NLB_THREADS) {
-    const int c = find_cell(s_home, 0, nhc, h);
-    const int ly = c / tg.nh, lx = c - ly * tg.nh;
-    const int t = (WY + ly + 1) * W + lx + 1;
-    const int r = h - s_home[c];
+    int lx, ly, t, r;
+    if (staged) {
+      const int m = s_hmap[h];
+      lx = (m & 255) - 1;
+      ly = (m >> 8) - 1;
+      t = (WY + ly + 1) * W + lx + 1;
+      r = h - s_home[ly * tg.nh + lx];
+    } else {
+      const int c = find_cell(s_home, 0, nhc, h);
+      ly = c / tg.nh;
+      lx = c - ly * tg.nh;
+      t = (WY + ly + 1) * W + lx + 1;
+      r = h - s_home[c];
+    }
     const int si = s_off[t] + r;
     const int g = first + h;
-    Staged<float> me;
-    if (staged) me = s_pos[si];
-    else me = make(t, member_slot(a, s_sc[t], s_off[t + 1] - s_off[t], r));
-    const int old = me.tag;
+    auto make = [&](int c, int sl) {
+      double o[3];
+      origin(c, o);
+      return quant(a.x[sl], a.x[(size_t)NP + sl], a.x[2 * (size_t)NP + sl], o);
+    };
+    const int old = staged ? s_old[si] : member_slot(a, s_sc[t], s_off[t + 1] - s_off[t], r);
+    const uint2 me = staged ? s_pos[si] : make(t, old);
     // the new slot takes the monomer's state: its loads are issued here and stored after the
     // list is built, so that they arrive while the list is built
     const int cx = wrapc(tg.x0 + lx, nc), cy = wrapc(tg.y0 + ly, nc), cz = tg.cz;
@@ -546,9 +603,11 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
     const int mo = a.mono[old];
     int n;
     if (staged)
-      n = nl_list_one(a, g, me, si, lx + 1, ly + 1, W, WY, hlr, rl2, rskip2, s_off, total, [&](int u) { return s_pos[u]; });
+      n = nl_list_one(a, g, me, si, lx + 1, ly + 1, W, WY, (float)U, minus_r2, rskip2, s_off, total,
+                      [&](int u, int) { return s_pos[u]; });
     else
-      n = nl_list_one(a, g, me, si, lx + 1, ly + 1, W, WY, hlr, rl2, rskip2, s_off, total, [&](int u) {
+      n = nl_list_one(a, g, me, si, lx + 1, ly + 1, W, WY, (float)U, minus_r2, rskip2, s_off, total, [&](int u, int e) {
+        u = min(u, e - 1);
         const int q = find_cell(s_off, 0, ncell, u);
         return make(q, member_slot(a, s_sc[q], s_off[q + 1] - s_off[q], u - s_off[q]));
       });
@@ -1054,7 +1113,7 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_step(NlArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
-size_t nl_stage_bytes(int, int cap) { return (size_t)(cap + 4) * sizeof(Staged<float>); }
+size_t nl_stage_bytes(int, int cap) { return (size_t)(cap + RB_PAD) * (sizeof(uint2) + sizeof(int) + sizeof(uint16_t)); }
 size_t rel_bytes(int prec) { return prec ? sizeof(Rel<float>::T) : sizeof(Rel<double>::T); }
 
 void launch_nl_rebuild(int prec, const NlArgs& a, int pblk, int ntile, bool bin, hipStream_t s) {
