@@ -94,8 +94,7 @@ struct kgdb_batch {
   int* d_cntl = nullptr;           // binning: count per sorted list-grid cell
   int* d_tcnt = nullptr;           // binning: count per tile
   int* d_tstart = nullptr;         // first slot of each tile
-  int* d_bucketl_raw = nullptr;    // slots binned into each cell
-  int* d_bucketl_mono = nullptr;   // and their monomer ids
+  int4* d_bucketl = nullptr;       // members binned into each cell
   int2* d_cellsc = nullptr;        // first slot and count of each sorted cell
   int* d_stage = nullptr;          // per tile: slots of its staged members (stage_cap_max each)
   int stage_cap_max = 0;           // LDS limit of a stage (members)
@@ -271,6 +270,7 @@ static void set_tile_shape(MeltDesc& d, TileShape t) {
   d.nl_nseg = (d.ncl + t.S - 1) / t.S;
   d.nl_Sy = t.Sy;
   d.nl_nyb = (d.ncl + t.Sy - 1) / t.Sy;
+  d.nl_u = 65535 / std::max(std::max(t.S, t.Sy) + 2, 6);
 }
 // whether (S, Sy) is a tile shape of melt d's list grid whose stage fits the LDS
 static bool tile_shape_ok(const MeltDesc& d, int precision, TileShape t) {
@@ -294,6 +294,8 @@ static void set_list_geometry(MeltDesc& d, const kgdb_params& p, int K, double n
   d.rc2_fx = d.rc2 / (u * u);
   d.iu2_fx = 1.0 / (u * u);
   d.rlist2 = rl * rl;
+  // cells of more than 6.5 members on average: a group of 8 lanes would leave one in five to the slow path
+  d.nl_wide = (double)d.Nm / ((double)d.ncl * d.ncl * d.ncl) > 6.5 ? 1 : 0;
   d.half_skin2 = 0.25 * skin * skin;
   d.half_skin = 0.5 * skin;
   std::vector<TileShape> sh;
@@ -510,8 +512,7 @@ static NlArgs nl_args(kgdb_batch* b) {
   a.cnt = b->d_cntl;
   a.tcnt = b->d_tcnt;
   a.tstart = b->d_tstart;
-  a.bucket_raw = b->d_bucketl_raw;
-  a.bucket_mono = b->d_bucketl_mono;
+  a.bucket = b->d_bucketl;
   a.cellsc = b->d_cellsc;
   a.stage_list = b->d_stage;
   a.stage_stride = b->stage_cap_max;
@@ -1199,8 +1200,7 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
   step(dalloc(b, &b->d_nlstat, 2));
   step(dalloc(b, &b->d_stage, std::max<size_t>(b->stage_words, 1)));
   step(dalloc(b, &b->d_smeta, (size_t)b->NTILE));
-  step(dalloc(b, &b->d_bucketl_raw, (size_t)b->NCL * NL_CELL_CAP));
-  step(dalloc(b, &b->d_bucketl_mono, (size_t)b->NCL * NL_CELL_CAP));
+  step(dalloc(b, &b->d_bucketl, (size_t)b->NCL * NL_CELL_CAP));
   step(dalloc(b, &b->d_disp, 2 * (size_t)DISP_SLOTS * DISP_STRIDE * count));
   step(dalloc(b, &b->d_dacc, (size_t)count));
   step(dalloc(b, &b->d_floor, (size_t)count));

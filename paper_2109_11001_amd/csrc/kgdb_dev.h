@@ -73,6 +73,8 @@ struct MeltDesc {
   // list build: each workgroup takes a block of nl_S x nl_Sy cells of one z-plane of the list
   // grid (nl_nseg blocks along x, nl_nyb along y) and stages its neighbourhood in LDS
   int nl_S, nl_Sy, nl_nseg, nl_nyb;
+  int nl_u;                  // units per cell edge of a rebuild's 16-bit frame positions
+  int nl_wide;               // a rebuild reads a cell's members with 16 lanes instead of 8
   // initial state: KGDB_INIT_* and, for freely rotating chains, cos theta* (Eqs. 12-13)
   int init_mode;
   double fr_cos;

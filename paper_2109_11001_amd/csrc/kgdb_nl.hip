@@ -28,6 +28,8 @@
 // it is redone by the host with more frequent rebuilds.
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "kgdb_dev.h"
 #include "kgdb_kernels.h"
 
@@ -195,22 +197,27 @@ __device__ __forceinline__ int run_add(int* ctr, int key) {
   return base + (lane - hl);
 }
 
+// A bucket entry holds all that a rebuild stages of a member: its slot, its monomer id and its place in
+// the cell in units of 1 / nl_u of the cell's edge (x in the low, y in the high half of the third word).
 __device__ __forceinline__ void nl_bin_one(const NlArgs& a, int k, const MeltDesc& d, int g, int mono, double x,
                                            double y, double z, bool valid) {
   int sc = -1, tile = -1;
+  uint32_t oxy = 0, oz = 0;
   if (valid) {
-    const int nc = d.ncl;
-    sc = sorted_cell(d, cell_coord(x, d.cinvl, nc), cell_coord(y, d.cinvl, nc), cell_coord(z, d.cinvl, nc), &tile);
+    const int nc = d.ncl, U = d.nl_u;
+    const int cx = cell_coord(x, d.cinvl, nc), cy = cell_coord(y, d.cinvl, nc), cz = cell_coord(z, d.cinvl, nc);
+    sc = sorted_cell(d, cx, cy, cz, &tile);
+    auto place = [&](double w, int c) {
+      return (uint32_t)min(max((int)__builtin_fma(__builtin_fma(w, d.cinvl, -(double)c), (double)U, 0.5), 0), U);
+    };
+    oxy = place(x, cx) | (place(y, cy) << 16);
+    oz = place(z, cz);
   }
   const int s = run_add(a.cnt, sc);
   (void)run_add(a.tcnt, tile);
   if (!valid) return;
-  if (s < NL_CELL_CAP) {
-    a.bucket_raw[sc * NL_CELL_CAP + s] = g;
-    a.bucket_mono[sc * NL_CELL_CAP + s] = mono;
-  } else {
-    atomicOr(&a.err[k], ERR_CELL_OVERFLOW);
-  }
+  if (s < NL_CELL_CAP) a.bucket[(size_t)sc * NL_CELL_CAP + s] = make_int4(g, mono, (int)oxy, (int)oz);
+  else atomicOr(&a.err[k], ERR_CELL_OVERFLOW);
 }
 
 __global__ __launch_bounds__(256) void k_nl_bin(NlArgs a) {
@@ -286,12 +293,17 @@ __device__ __forceinline__ int find_cell(const int* s, int lo, int hi, int v) {
 }
 
 constexpr int NLB_CELLS = 594;  // staged cells: 3 (nl_S + 2)(nl_Sy + 2) <= 594
+constexpr int NLB_HOMES = 198;  // home cells: nl_S nl_Sy < (nl_S + 2)(nl_Sy + 2) <= 198
 // batches of at most this many list tiles find a tile's first slot inside the rebuild kernel
 constexpr int TILE_SUM_MAX = 4096;
-// bucket entries of a staged cell that its thread requests before it knows the cell's count; a cell
-// with more (rare: a cell of the longest interval holds about five) is ranked by a wavefront instead
-constexpr int RB_PF = 12;
-constexpr int RB_PAD = 8;  // staged entries past the capacity (a row is tested four members at a time)
+// A staged cell's members are read and ranked by a group of 8 lanes, an entry a lane, in melts of many
+// members a cell (nl_wide: the smallest boxes, eight a cell) by 16; a cell with more goes to a
+// wavefront.  (A cell a thread touched 64 cache lines with each of its loads.)
+constexpr int RB_ROW = 20;  // candidates of a row tested at once (a row holds about fifteen)
+// home members of a stage of `cap`: their mean is below a third of the stage's
+constexpr int RB_HOME_PAD = 64;
+__host__ __device__ constexpr int rb_home_cap(int cap) { return cap / 3 + RB_HOME_PAD; }
+constexpr int RB_PAD = 32;  // staged entries past the capacity (a row is read up to its 32nd candidate)
 
 // 16-byte word q (eight 16-bit entries) of the list of the monomer in slot i
 __device__ __forceinline__ size_t nl_word(int i, int q) {
@@ -301,14 +313,14 @@ __device__ __forceinline__ size_t nl_word(int i, int q) {
 // ---------------------------------------------------------------------------------------
 // rebuild 3: per tile, stage, move the home members to their new slots, list
 // ---------------------------------------------------------------------------------------
-// The members of staged cell t sorted by monomer id: slot of the member of rank r.
-__device__ __forceinline__ int member_slot(const NlArgs& a, int sc, int n, int r) {
-  const int* b = a.bucket_raw + (size_t)sc * NL_CELL_CAP;
+// The members of staged cell t sorted by monomer id: bucket entry of the member of rank r.
+__device__ __forceinline__ int4 member_entry(const NlArgs& a, int sc, int n, int r) {
+  const int4* b = a.bucket + (size_t)sc * NL_CELL_CAP;
   for (int j = 0; j < n; ++j) {
-    const int sj = b[j], mj = a.mono[sj];
+    const int4 e = b[j];
     int rank = 0;
-    for (int m = 0; m < n; ++m) rank += a.mono[b[m]] < mj;
-    if (rank == r) return sj;
+    for (int m = 0; m < n; ++m) rank += b[m].y < e.y;
+    if (rank == r) return e;
   }
   return b[0];
 }
@@ -326,77 +338,176 @@ __device__ __forceinline__ int quant_test(uint2 p, uint2 me, int minus_r2) {  //
   return __builtin_amdgcn_sdot2(xy, xy, __builtin_amdgcn_sdot2(z, z, minus_r2, false), false);
 }
 
+// frame position of a bucket entry of staged cell (i, yy, zz)
+__device__ __forceinline__ uint2 quant_pos(int4 e, int i, int yy, int zz, int U) {
+  return make_uint2((uint32_t)e.z + (uint32_t)(i * U) + ((uint32_t)(yy * U) << 16), (uint32_t)(e.w + zz * U));
+}
+
 // The list of one home monomer (staged position me, staged index tme, home cell (ih, yy) of
 // the frame): staged members within r_list in the 3 x 3 rows of three cells around it.  A
 // row, or a side cell of it, whose nearest point is beyond r_list plus a margin holds no member
-// within r_list and is skipped.  at(t) gives staged member t (read up to three past a row's end).
+// within r_list and is skipped.
 //
-// A row's candidates are tested into a bit mask, then its set bits are stored: the test is then free
-// of the bookkeeping of an entry (28 instructions a candidate when each was stored as it was found,
-// 7 now; a list takes a seventh of its candidates).  Entry j of slot g lies in word nl_word(g, j / 8)
-// at place j % 8.  The last word is filled up with `pad`, the index one past the stage, where the
-// step keeps a position outside every cutoff: the step reads whole words without testing the list's end.
-template <typename At>
-__device__ __forceinline__ int nl_list_one(const NlArgs& a, int g, uint2 me, int tme, int ih, int yy, int W, int WY,
-                                           float U, int minus_r2, float rskip2, const int* s_off, int pad, At at) {
-  uint16_t* __restrict__ out = (uint16_t*)a.nlist + nl_word(g, 0) * 8;
-  int cnt = 0;
+// A row's candidates are tested into a bit mask, so that the tests are free of the bookkeeping of an
+// entry (a list takes a seventh of its candidates), and all rows' bounds, then a row's candidates, are
+// requested before any is used.  The set bits then go to the thread's run in LDS, a row's first and last
+// ones at a time (its count of bits says where its entries end), and the list leaves as whole 16-byte
+// words.  A list of more than LB_CAP entries (it holds 19 on average) is stored entry by entry instead.
+// Entry j of slot g lies in word nl_word(g, j / 8) at place j % 8; the last word is filled up with
+// `pad`, the index one past the stage, where the step keeps a position outside every cutoff: the step
+// reads whole words without testing the list's end.
+struct ListArgs {
+  int W, WY, U, minus_r2;
+  float rskip2;
+  const int* s_off;
+  int pad;
+};
+constexpr int LB_CAP = 32;
+constexpr int LB_STRIDE = 2 * LB_CAP + 4;  // bytes of a thread's run: lanes fall on different banks
+// candidates [b, b + n) of row r = 3 zz + dy + 1
+__device__ __forceinline__ void list_row(const ListArgs& l, uint2 me, int ih, int yy, int r, int& bi, int& ei) {
+  const float U = (float)l.U;
   const float dxl = (float)(me.x & 0xffffu) - (float)ih * U, dxr = U - dxl;
   const float dyl = (float)(me.x >> 16) - (float)yy * U, dyr = U - dyl;
   const float dzl = (float)me.y - U, dzr = U - dzl;
-  for (int zz = 0; zz < 3; ++zz) {
-    const float ez = zz == 0 ? dzl : (zz == 2 ? dzr : 0.0f);
-    for (int dy = -1; dy <= 1; ++dy) {
-      const float ey = dy < 0 ? dyl : (dy > 0 ? dyr : 0.0f);
-      const float e2 = ey * ey + ez * ez;
-      const int c0 = (zz * WY + yy + dy) * W + ih - 1;  // cells c0 .. c0 + 2: x offsets -1, 0, +1
-      int b = s_off[c0], e = s_off[c0 + 3];
-      if (e2 > rskip2) {
-        e = b;
-      } else {
-        if (dxl * dxl + e2 > rskip2) b = s_off[c0 + 1];
-        if (dxr * dxr + e2 > rskip2) e = s_off[c0 + 2];
+  const int zz = r / 3, dy = r % 3 - 1;
+  const float ez = zz == 0 ? dzl : (zz == 2 ? dzr : 0.0f), ey = dy < 0 ? dyl : (dy > 0 ? dyr : 0.0f);
+  const float e2 = ey * ey + ez * ez;
+  const int c0 = (zz * l.WY + yy + dy) * l.W + ih - 1;  // cells c0 .. c0 + 2: x offsets -1, 0, +1
+  bi = c0 + (dxl * dxl + e2 > l.rskip2 ? 1 : 0);
+  ei = e2 > l.rskip2 ? bi : c0 + (dxr * dxr + e2 > l.rskip2 ? 2 : 3);
+}
+// the list entry by entry, members through at(t)
+template <typename At>
+__device__ __forceinline__ int nl_list_any(const NlArgs& a, const ListArgs& l, int g, uint2 me, int tme, int ih, int yy, At at) {
+  uint16_t* __restrict__ out = (uint16_t*)a.nlist + nl_word(g, 0) * 8;
+  int cnt = 0;
+  for (int r = 0; r < 9; ++r) {
+    int bi, ei;
+    list_row(l, me, ih, yy, r, bi, ei);
+    const int e = l.s_off[ei];
+    for (int t = l.s_off[bi]; t < e; ++t)
+      if (t != tme && quant_test(at(t), me, l.minus_r2) < 0) {
+        if (cnt < NL_CAP) out[(cnt >> 3) * 512 + (cnt & 7)] = (uint16_t)t;
+        ++cnt;
       }
-      for (int s0 = b; s0 < e; s0 += 32) {  // (a row holds about fifteen)
-        const int n = min(e - s0, 32);
-        uint32_t mask = 0;
-        int t = 0;
-        for (; t < n; t += 4) {
-          uint2 p[4];
+  }
+  for (int c = cnt; c < NL_CAP && (c & 7); ++c) out[(c >> 3) * 512 + (c & 7)] = (uint16_t)l.pad;
+  return cnt;
+}
+__device__ __forceinline__ int nl_list_one(const NlArgs& a, const ListArgs& l, int g, uint2 me, int tme, int ih, int yy,
+                                           unsigned char* s_list, const uint2* s_pos) {
+  int b[9], n[9], nmax = 0;
 #pragma unroll
-          for (int u = 0; u < 4; ++u) p[u] = at(s0 + t + u, e);
+  for (int r = 0; r < 9; ++r) {
+    int bi, ei;
+    list_row(l, me, ih, yy, r, bi, ei);
+    b[r] = l.s_off[bi];
+    n[r] = l.s_off[ei];
+  }
 #pragma unroll
-          for (int u = 0; u < 4; ++u)  // shift the test's sign bit in
-            mask = __builtin_amdgcn_alignbit(mask, (uint32_t)quant_test(p[u], me, minus_r2), 31);
-        }
-        mask <<= 32 - t;                   // candidate s0 at bit 31
-        mask &= 0xffffffffu << (32 - n);   // none past the row
-        const uint32_t self = (uint32_t)(tme - s0);
-        if (self < 32u) mask &= ~(0x80000000u >> self);
-        while (mask) {
-          const int u = __builtin_clz(mask);
-          mask &= ~(0x80000000u >> u);
-          if (cnt < NL_CAP) out[(cnt >> 3) * 512 + (cnt & 7)] = (uint16_t)(s0 + u);
-          ++cnt;
-        }
-      }
+  for (int r = 0; r < 9; ++r) {
+    n[r] -= b[r];
+    nmax = max(nmax, n[r]);
+  }
+  uint32_t m[9];
+  int cnt = 0;
+#pragma unroll
+  for (int r = 0; r < 9; ++r) {
+    uint2 p[RB_ROW];
+#pragma unroll
+    for (int u = 0; u < RB_ROW; ++u) p[u] = s_pos[b[r] + u];
+    uint32_t mask = 0;
+#pragma unroll
+    for (int u = 0; u < RB_ROW; ++u)  // shift the test's sign bit in
+      mask = __builtin_amdgcn_alignbit(mask, (uint32_t)quant_test(p[u], me, l.minus_r2), 31);
+    mask <<= 32 - RB_ROW;
+    if (__ballot(n[r] > RB_ROW)) {
+      uint32_t more = 0;
+#pragma unroll
+      for (int u = RB_ROW; u < 32; ++u)
+        more = __builtin_amdgcn_alignbit(more, (uint32_t)quant_test(s_pos[b[r] + u], me, l.minus_r2), 31);
+      mask |= more;
+    }
+    // none past the row, nor the monomer itself
+    mask = n[r] > 0 ? mask & (0xffffffffu << (32 - n[r])) : 0u;
+    if (r == 4) mask &= ~(0x80000000u >> (tme - b[r]));
+    m[r] = mask;
+    cnt += __popc(mask);
+  }
+  if (cnt > LB_CAP || nmax > 32)
+    return nl_list_any(a, l, g, me, tme, ih, yy, [&](int t) { return s_pos[t]; });
+  unsigned char* const buf = s_list + threadIdx.x * LB_STRIDE;
+  unsigned char* front = buf;
+#pragma unroll
+  for (int r = 0; r < 9; ++r) {
+    uint32_t mask = m[r];
+    unsigned char *f = front, *e = front + 2 * __popc(mask);
+    front = e;
+    while (mask) {
+      const int u = __builtin_clz(mask), v = 31 - __builtin_ctz(mask);
+      e -= 2;
+      *(uint16_t*)f = (uint16_t)(b[r] + u);
+      *(uint16_t*)e = (uint16_t)(b[r] + v);
+      f += 2;
+      mask &= ~((0x80000000u >> u) | (0x80000000u >> v));
     }
   }
-  for (int c = cnt; c < NL_CAP && (c & 7); ++c) out[(c >> 3) * 512 + (c & 7)] = (uint16_t)pad;
+  const int words = (cnt + 7) >> 3;
+  for (int c = cnt; c < 8 * words; ++c) *(uint16_t*)(buf + 2 * c) = (uint16_t)l.pad;
+  uint4* __restrict__ out = (uint4*)a.nlist + nl_word(g, 0);
+#pragma unroll
+  for (int w = 0; w < LB_CAP / 8; ++w)
+    if (w < words) {
+      const uint32_t* p = (const uint32_t*)(buf + 16 * w);
+      out[w * 64] = make_uint4(p[0], p[1], p[2], p[3]);
+    }
   return cnt;
 }
 
+// One workgroup per tile, all resident at once at 200,000 monomers (952 tiles, 3.7 a CU: 128 registers and
+// a quarter of a CU's LDS each), so the launch lasts as long as its slowest tile.  Bound by latency: the
+// counts and members of the staged cells arrive in 5 + 6 us there (2.5 + 3 us on an idle chip), the
+// lists take 6-8 us.  1,000 monomers 18 us, 50,000 21 us, 200,000 39 us, 1M 126 us; with a thread per
+// cell, per-entry stores and FP32 positions gathered by slot 38, 41, 58 and 222 us.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+// number of the other lanes of a group of G (8 or 16) whose v is smaller.  Within four lanes, lane ^ 1, 2
+// and 3 are quad permutations; a half row and a row reversed give lane ^ 7 and ^ 15.
+template <int G>
+__device__ __forceinline__ int group_rank(int v) {
+  int r = 0;
+  auto quad = [&](int w) {  // w and its three quad neighbours
+    r += (w < v) + (dpp<0xB1>(w) < v) + (dpp<0x4E>(w) < v) + (dpp<0x1B>(w) < v);
+  };
+  quad(v);  // (v < v counts nothing)
+  quad(dpp<0x141>(v));
+  if constexpr (G == 16) {
+    const int m = dpp<0x140>(v);
+    quad(m);
+    quad(dpp<0x141>(m));
+  }
+  return r;
+}
+
 template <typename R>
-__global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
+__global__ __launch_bounds__(NLB_THREADS, 4) void k_nl_rebuild(NlArgs a) {
   extern __shared__ __align__(16) unsigned char s_dyn[];
-  uint2* const s_pos = (uint2*)s_dyn;                             // staged members, by cell and monomer id
-  int* const s_old = (int*)(s_pos + a.stage_cap + RB_PAD);        // their old slots
-  uint16_t* const s_hmap = (uint16_t*)(s_old + a.stage_cap + RB_PAD);  // home cell of each home: y << 8 | x of the frame
+  uint2* const s_pos = (uint2*)s_dyn;                     // staged members, by cell and monomer id
+  const int hcap = rb_home_cap(a.stage_cap);
+  int* const s_old = (int*)(s_pos + a.stage_cap + RB_PAD);  // old slots of the home members
+  uint16_t* const s_hmap = (uint16_t*)(s_old + hcap);       // and their home cell: y << 8 | x of the frame
+  // the threads' lists; before they are begun, the cells' sorted indices and the cells left to a wavefront
+  // (a workgroup's LDS then stays below a quarter of a CU's at the usual stages)
+  __shared__ __align__(4) unsigned char s_list[NLB_THREADS * LB_STRIDE];
+  int* const s_sc = (int*)s_list;
+  int* const s_geo = s_sc + NLB_CELLS;  // x | y << 8 | z << 16 of a frame cell
+  uint16_t* const s_big = (uint16_t*)(s_geo + NLB_CELLS);
+  static_assert(NLB_CELLS * 10 <= NLB_THREADS * LB_STRIDE, "fits");
   __shared__ int s_off[NLB_CELLS + 1];
-  __shared__ int s_sc[NLB_CELLS];
-  __shared__ int s_home[NLB_CELLS + 1];  // prefix of the home cells' counts, sorted order
-  __shared__ uint8_t s_wrap[NLB_CELLS];  // per staged cell and axis: periodic wrap -1, 0, +1 (2 bits each, +1)
-  __shared__ uint16_t s_big[NLB_CELLS];  // cells of more than RB_PF members
+  __shared__ int s_home[NLB_HOMES + 1];  // prefix of the home cells' counts, sorted order
   __shared__ int s_nbig;
   const int lb = xcd_remap(blockIdx.x, gridDim.x);
   const int k = __builtin_amdgcn_readfirstlane(a.rblk_melt[lb]);
@@ -406,22 +517,8 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
   const int W = tg.nh + 2, WY = tg.nhy + 2, ncell = 3 * WY * W;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const double hl = d.hl;
-  const int nc = d.ncl;
-  // units per cell edge, and per unit length
-  const int U = 65535 / max(max(W, WY), 6);
-  const double qs = (double)U / hl;
+  const int nc = d.ncl, U = d.nl_u;
 
-  int id[RB_PF], slot[RB_PF];
-  auto fetch = [&](int sc) {
-    const int4* bm = (const int4*)(a.bucket_mono + (size_t)sc * NL_CELL_CAP);
-    const int4* br = (const int4*)(a.bucket_raw + (size_t)sc * NL_CELL_CAP);
-#pragma unroll
-    for (int q = 0; q < RB_PF / 4; ++q) {
-      const int4 m = bm[q], r = br[q];
-      id[4 * q] = m.x; id[4 * q + 1] = m.y; id[4 * q + 2] = m.z; id[4 * q + 3] = m.w;
-      slot[4 * q] = r.x; slot[4 * q + 1] = r.y; slot[4 * q + 2] = r.z; slot[4 * q + 3] = r.w;
-    }
-  };
   // the first slot of this tile: with few tiles in the batch, the sum of the counts of the tiles
   // before it, read here with the cells' counts (no scan kernel); else the scan's result
   const int tile = d.tile_off + lt;
@@ -433,14 +530,11 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
     const StagedCell s = staged_cell(d, tg, W, WY, t);
     const int sc = sorted_cell(d, s.ax, s.ay, s.az, nullptr);
     const int n = min(a.cnt[sc], NL_CELL_CAP);
-    // (a thread's first cell: its members' ids and slots arrive with the count)
-    if (t == (int)threadIdx.x) fetch(sc);
     s_sc[t] = sc;
+    s_geo[t] = s.i | s.yy << 8 | s.zz << 16;
     s_off[t + 1] = n;
     if (s.zz == 1 && s.yy >= 1 && s.yy <= tg.nhy && s.i >= 1 && s.i <= tg.nh)
       s_home[(s.yy - 1) * tg.nh + s.i] = n;
-    const int wx = s.ax - (tg.x0 - 1 + s.i), wy = s.ay - (tg.y0 - 1 + s.yy), wz = s.az - (tg.cz - 1 + s.zz);
-    s_wrap[t] = (uint8_t)((wx > 0) - (wx < 0) + 1 + (((wy > 0) - (wy < 0) + 1) << 2) + (((wz > 0) - (wz < 0) + 1) << 4));
   }
   if (tile_sum) {
     int part = 0;
@@ -450,98 +544,71 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
     if (lane == 0) s_tsum[wv] = part;
   }
   __syncthreads();
+  // (the members arrive while the counts' prefixes are formed)
+  constexpr int BATCH = 8;  // cells a group takes at once
+  int4 ent[BATCH];
+  const bool wide = d.nl_wide;
+  auto fetch = [&](int g, int c0) {  // lanes of a group, first cell of its batch
+    const int per = NLB_THREADS / g;
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int c = min(c0 + i * per + (int)threadIdx.x / g, ncell - 1);
+      ent[i] = a.bucket[(size_t)s_sc[c] * NL_CELL_CAP + (threadIdx.x & (g - 1))];
+    }
+  };
+  if (wide) fetch(16, 0);
+  else fetch(8, 0);
   if (wv == 0) wave_prefix(s_off, ncell);
   if (wv == 1) wave_prefix(s_home, nhc);
   __syncthreads();
   const int total = s_off[ncell], nhome = s_home[nhc];
-  const bool staged = total <= a.stage_cap && !(d.test_flags & TF_NL_GLOBAL);
+  const bool staged = total <= a.stage_cap && nhome <= hcap && !(d.test_flags & TF_NL_GLOBAL);
   if (threadIdx.x == 0 && !(d.test_flags & TF_NL_GLOBAL) && a.nlstat) {
-    atomicMax(&a.nlstat[1], (uint32_t)total);
+    // (a capacity of the reported size holds the stage and, as a third of it, the homes)
+    atomicMax(&a.nlstat[1], (uint32_t)max(total, 3 * (nhome - RB_HOME_PAD)));
     if (!staged) atomicAdd(&a.nlstat[0], 1u);
   }
-  // staged member of cell t: its frame position (the frame's cell (i, yy, zz) is grid cell
-  // (x0 - 1 + i, y0 - 1 + yy, cz - 1 + zz) up to the recorded periodic wrap, so that the frame origin
-  // of a member is (x0 - 1, y0 - 1, cz - 1) + wrap nc), rounded to units
-  auto origin = [&](int t, double o[3]) {
-    const int f = s_wrap[t];
-    o[0] = 0.5 - (double)(tg.x0 - 1 + ((f & 3) - 1) * nc) * U;
-    o[1] = 0.5 - (double)(tg.y0 - 1 + (((f >> 2) & 3) - 1) * nc) * U;
-    o[2] = 0.5 - (double)(tg.cz - 1 + ((f >> 4) - 1) * nc) * U;
-  };
-  auto quant = [&](double x, double y, double z, const double o[3]) {
-    const int qx = (int)__builtin_fma(x, qs, o[0]), qy = (int)__builtin_fma(y, qs, o[1]), qz = (int)__builtin_fma(z, qs, o[2]);
-    return make_uint2((uint32_t)min(max(qx, 0), 65535) | ((uint32_t)min(max(qy, 0), 65535) << 16),
-                      (uint32_t)min(max(qz, 0), 32767));
-  };
   const int NP = a.NP;
   if (staged) {
-    // a cell a thread: each member's rank by id gives its place in the stage
-    for (int t = threadIdx.x; t < ncell; t += NLB_THREADS) {
-      const int b0 = s_off[t], n = s_off[t + 1] - b0;
-      if (t != (int)threadIdx.x) fetch(s_sc[t]);
-      const int row = t / W, ih = t - row * W, zz = row / WY, yy = row - zz * WY;
-      if (zz == 1 && yy >= 1 && yy <= tg.nhy && ih >= 1 && ih <= tg.nh) {
-        const int h0 = s_home[(yy - 1) * tg.nh + ih - 1];
-        for (int j = 0; j < n; ++j) s_hmap[h0 + j] = (uint16_t)(yy << 8 | ih);
+    // each member's rank by id within its cell gives its place in the stage
+    auto put = [&](int c, int b0, int r, const int4& e) {
+      const int geo = s_geo[c], i = geo & 255, yy = (geo >> 8) & 255, zz = geo >> 16;
+      s_pos[b0 + r] = quant_pos(e, i, yy, zz, U);
+      if (zz == 1 && yy >= 1 && yy <= tg.nhy && i >= 1 && i <= tg.nh) {
+        const int h = s_home[(yy - 1) * tg.nh + i - 1] + r;
+        s_old[h] = e.x;
+        s_hmap[h] = (uint16_t)(yy << 8 | i);
       }
-      if (n > RB_PF) {
-        s_big[atomicAdd(&s_nbig, 1)] = (uint16_t)t;
-        continue;
-      }
-      int r[RB_PF];
+    };
+    auto stage = [&](auto gw) {
+      constexpr int g = decltype(gw)::value, per = NLB_THREADS / g;
+      const int j = threadIdx.x & (g - 1);
+      for (int c0 = 0; c0 < ncell; c0 += BATCH * per) {
+        if (c0) fetch(g, c0);
 #pragma unroll
-      for (int j = 0; j < RB_PF; ++j) {
-        id[j] = j < n ? id[j] : 0x7fffffff;
-        slot[j] = j < n ? slot[j] : d.off;
-        r[j] = b0;
-      }
-      auto rank = [&](int m) {  // among the first m
-#pragma unroll
-        for (int j = 0; j < RB_PF; ++j)
-#pragma unroll
-          for (int q = j + 1; q < RB_PF; ++q)
-            if (q < m) {
-              const int lt2 = id[j] < id[q];
-              r[q] += lt2;
-              r[j] += 1 - lt2;
-            }
-      };
-      if (__ballot(n > 8)) rank(RB_PF);
-      else rank(8);
-      double o[3];
-      origin(t, o);
-#pragma unroll
-      for (int q = 0; q < RB_PF / 4; ++q) {
-        if (!__ballot(n > 4 * q)) break;
-        double x[4], y[4], z[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          x[j] = a.x[slot[4 * q + j]];
-          y[j] = a.x[(size_t)NP + slot[4 * q + j]];
-          z[j] = a.x[2 * (size_t)NP + slot[4 * q + j]];
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (4 * q + j < n) {
-            s_pos[r[4 * q + j]] = quant(x[j], y[j], z[j], o);
-            s_old[r[4 * q + j]] = slot[4 * q + j];
+        for (int i = 0; i < BATCH; ++i) {
+          const int c = c0 + i * per + (int)threadIdx.x / g;
+          if (c0 + i * per >= ncell) break;  // (uniform)
+          const int cc = min(c, ncell - 1), b0 = s_off[cc], n = c < ncell ? s_off[cc + 1] - b0 : 0;
+          const int r = group_rank<g>(j < n ? ent[i].y : 0x7fffffff);
+          if (n > g) {
+            if (j == 0) s_big[atomicAdd(&s_nbig, 1)] = (uint16_t)c;
+          } else if (j < n) {
+            put(c, b0, r, ent[i]);
           }
+        }
       }
-    }
+    };
+    if (wide) stage(std::integral_constant<int, 16>{});
+    else stage(std::integral_constant<int, 8>{});
     __syncthreads();
     const int nbig = s_nbig;
     for (int q = wv; q < nbig; q += NLB_THREADS / 64) {  // a member a lane
       const int t = s_big[q], b0 = s_off[t], n = s_off[t + 1] - b0;
-      const size_t e = (size_t)s_sc[t] * NL_CELL_CAP + min(lane, n - 1);
-      const int me = a.bucket_mono[e], sl = a.bucket_raw[e];
+      const int4 e = a.bucket[(size_t)s_sc[t] * NL_CELL_CAP + min(lane, n - 1)];
       int r = 0;
-      for (int m = 0; m < n; ++m) r += __shfl(me, m, 64) < me;
-      double o[3];
-      origin(t, o);
-      if (lane < n) {
-        s_pos[b0 + r] = quant(a.x[sl], a.x[(size_t)NP + sl], a.x[2 * (size_t)NP + sl], o);
-        s_old[b0 + r] = sl;
-      }
+      for (int m = 0; m < n; ++m) r += __shfl(e.y, m, 64) < e.y;
+      if (lane < n) put(t, b0, r, e);
     }
     if (nbig) __syncthreads();
   }
@@ -557,9 +624,9 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
     const int t = (WY + ly + 1) * W + lx + 1;
     a.cellsc[s_sc[t]] = make_int2(first + s_home[c], s_home[c + 1] - s_home[c]);
   }
-  const float rl = (float)(sqrt(d.rlist2 * 1.0002) * qs) + 2.0f, rsk = rl + 4.0f;
-  const int minus_r2 = -(int)(rl * rl) - 1;
-  const float rskip2 = rsk * rsk;
+  __syncthreads();  // (the staged list builder overwrites the cells' indices; the other one reads them)
+  const float rl = (float)(sqrt(d.rlist2 * 1.0002) * d.cinvl) * (float)U + 2.0f, rsk = rl + 4.0f;
+  const ListArgs la = {W, WY, U, -(int)(rl * rl) - 1, rsk * rsk, s_off, total};
   for (int h = threadIdx.x; h < nhome; h += NLB_THREADS) {
     int lx, ly, t, r;
     if (staged) {
@@ -577,39 +644,34 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
     }
     const int si = s_off[t] + r;
     const int g = first + h;
-    auto make = [&](int c, int sl) {
-      double o[3];
-      origin(c, o);
-      return quant(a.x[sl], a.x[(size_t)NP + sl], a.x[2 * (size_t)NP + sl], o);
-    };
-    const int old = staged ? s_old[si] : member_slot(a, s_sc[t], s_off[t + 1] - s_off[t], r);
-    const uint2 me = staged ? s_pos[si] : make(t, old);
+    int old;
+    uint2 me;
+    if (staged) {
+      old = s_old[h];
+      me = s_pos[si];
+    } else {
+      const int4 e = member_entry(a, s_sc[t], s_off[t + 1] - s_off[t], r);
+      old = e.x;
+      me = quant_pos(e, lx + 1, ly + 1, 1, U);
+    }
     // the new slot takes the monomer's state: its loads are issued here and stored after the
     // list is built, so that they arrive while the list is built
     const int cx = wrapc(tg.x0 + lx, nc), cy = wrapc(tg.y0 + ly, nc), cz = tg.cz;
-    double xo[3], vo[3], fco[3] = {0.0, 0.0, 0.0}, flo[3] = {0.0, 0.0, 0.0};
+    double xo[3], vo[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       xo[q] = a.x[(size_t)q * NP + old];
       vo[q] = a.v[(size_t)q * NP + old];
     }
-    if (a.perm_f) {
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        fco[q] = a.fc[(size_t)q * NP + old];
-        flo[q] = a.fl[(size_t)q * NP + old];
-      }
-    }
     const int mo = a.mono[old];
     int n;
     if (staged)
-      n = nl_list_one(a, g, me, si, lx + 1, ly + 1, W, WY, (float)U, minus_r2, rskip2, s_off, total,
-                      [&](int u, int) { return s_pos[u]; });
+      n = nl_list_one(a, la, g, me, si, lx + 1, ly + 1, s_list, s_pos);
     else
-      n = nl_list_one(a, g, me, si, lx + 1, ly + 1, W, WY, (float)U, minus_r2, rskip2, s_off, total, [&](int u, int e) {
-        u = min(u, e - 1);
+      n = nl_list_any(a, la, g, me, si, lx + 1, ly + 1, [&](int u) {
         const int q = find_cell(s_off, 0, ncell, u);
-        return make(q, member_slot(a, s_sc[q], s_off[q + 1] - s_off[q], u - s_off[q]));
+        const int row = q / W, i = q - row * W, zz = row / WY, yy = row - zz * WY;
+        return quant_pos(member_entry(a, s_sc[q], s_off[q + 1] - s_off[q], u - s_off[q]), i, yy, zz, U);
       });
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -619,8 +681,8 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_rebuild(NlArgs a) {
     if (a.perm_f) {
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
-        a.fcn[(size_t)q * NP + g] = fco[q];
-        a.fln[(size_t)q * NP + g] = flo[q];
+        a.fcn[(size_t)q * NP + g] = a.fc[(size_t)q * NP + old];
+        a.fln[(size_t)q * NP + g] = a.fl[(size_t)q * NP + old];
       }
     }
     a.mono_n[g] = mo;
@@ -1113,7 +1175,9 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_step(NlArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
-size_t nl_stage_bytes(int, int cap) { return (size_t)(cap + RB_PAD) * (sizeof(uint2) + sizeof(int) + sizeof(uint16_t)); }
+size_t nl_stage_bytes(int, int cap) {
+  return (size_t)(cap + RB_PAD) * sizeof(uint2) + (size_t)rb_home_cap(cap) * (sizeof(int) + sizeof(uint16_t));
+}
 size_t rel_bytes(int prec) { return prec ? sizeof(Rel<float>::T) : sizeof(Rel<double>::T); }
 
 void launch_nl_rebuild(int prec, const NlArgs& a, int pblk, int ntile, bool bin, hipStream_t s) {

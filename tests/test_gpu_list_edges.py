@@ -1,0 +1,49 @@
+"""The list rebuild where its fixed widths end: cells of more members than a group's 8 or 16 lanes,
+rows of more candidates than one (20) or two (32) tests at once take, lists longer than a thread's run
+in LDS (32), frames that wrap onto themselves, a tile remainder of one cell.  FP64 steps against the
+oracle, and the mixed path's staged build against its build from global memory."""
+import numpy as np
+import pytest
+
+from oracle import oracle as o
+from tests import inputs
+
+pytestmark = pytest.mark.gpu
+
+kg = pytest.importorskip("paper_2109_11001_amd")
+torch = pytest.importorskip("torch")
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+CASES = [
+    dict(M=20, N=50, rho=0.85),   # 5 cells a side, 8 members a cell (groups of 16), rows of 24
+    dict(M=20, N=50, rho=1.8),    # 4 cells a side, 16 a cell, rows of 47, lists of 40
+    dict(M=40, N=100, rho=1.3),   # rows of 24, lists of 29: some past 32
+    dict(M=100, N=100, rho=0.85),  # five a cell (groups of 8, some cells past it)
+    dict(M=37, N=61, rho=0.6),
+]
+
+
+@pytest.mark.parametrize("kw", CASES)
+def test_lists_at_the_edges(kw):
+    kw = dict(kw, kappa=1.0, seed=13)
+    om = o.Melt(warmup_steps=300, **kw)
+    st = om.get_state()
+    st["v"] = np.clip(inputs.random_velocities(kw["M"] * kw["N"], 5), -3.0, 3.0)
+    om.set_state(x=st["x"], v=st["v"], fl=st["fl"], chains=st["chains"], counters=st["counters"])
+    melts = {}
+    for name, more in (("fp64", dict(precision=0)), ("mixed", dict(precision=1)),
+                       ("global", dict(precision=1, test_flags=kg.TF_NL_GLOBAL))):
+        g = kg.Melt(warmup_steps=0, nl_every=5, **more, **kw)
+        g.set_state(0, x=st["x"], v=st["v"], fl=st["fl"], chains=st["chains"], counters=st["counters"])
+        g.md_steps(12)
+        melts[name] = g
+    om.md_steps(12)
+    d = melts["fp64"].get_state()["x"] - om.get_state()["x"]
+    d -= om.L * np.rint(d / om.L)
+    assert np.max(np.abs(d)) < 1e-11  # a short window of FP64 steps
+    a, b = melts["mixed"].get_state(), melts["global"].get_state()
+    assert np.array_equal(a["x"], b["x"]) and np.array_equal(a["v"], b["v"])
+    assert melts["mixed"].nl_info()["K"] == 5
+    assert melts["mixed"].nl_info()["mean_list"] == melts["global"].nl_info()["mean_list"]
