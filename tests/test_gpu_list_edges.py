@@ -47,3 +47,21 @@ def test_lists_at_the_edges(kw):
     assert np.array_equal(a["x"], b["x"]) and np.array_equal(a["v"], b["v"])
     assert melts["mixed"].nl_info()["K"] == 5
     assert melts["mixed"].nl_info()["mean_list"] == melts["global"].nl_info()["mean_list"]
+
+
+@pytest.mark.parametrize("shape", [(5, 5), (5, 3), (3, 5)])
+def test_frames_that_wrap_keep_their_stage(shape):
+    # 5 cells a side: frames of 7 cells hold some cells twice, in x, in y or in both; the record of
+    # their stage keeps which one a member is.  The mixed path equals the one that reads global memory
+    # at every step, bit for bit.
+    kw = dict(M=20, N=50, seed=3, kappa=1.0, warmup_steps=200, nl_every=5, precision=1)
+    flat, wrapped = kg.Melt(test_flags=kg.TF_NL_GLOBAL, **kw), kg.Melt(**kw)
+    wrapped.set_tiles(*shape)
+    for m in (flat, wrapped):
+        m.md_steps(60)
+        m.db_sweep(40)
+        m.md_steps(35)
+    assert wrapped.nl_stats()["stage_overflows"] == 0
+    s0, s1 = flat.get_state(), wrapped.get_state()
+    for f in ("x", "v", "fl", "fc", "chains"):
+        assert np.array_equal(s0[f], s1[f]), f
