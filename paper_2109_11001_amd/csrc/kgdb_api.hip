@@ -237,14 +237,41 @@ static double nl_skin_for(const kgdb_params& p, int K, double nm_total) {
   return p.nl_skin > 0 ? p.nl_skin : 2.0 * nl_skin_sigmas(nm_total) * K * p.dt * std::sqrt(p.T > 0 ? p.T : 1.0);
 }
 
-// Tiles of nl_S x nl_Sy cells, ranked by a model of their cost per home monomer.  A workgroup
-// stages 3 (nl_S + 2)(nl_Sy + 2) cells and updates its home monomers in rounds of NLB_THREADS
-// lanes (a round costs the same whether or not every lane holds a monomer); the last tile of a
-// row (column) takes the remainder, and no tile is empty.  The stage must fit the LDS cap with
-// room for fluctuations.  out receives up to nmax shapes, cheapest first.
-static void tile_shapes(const MeltDesc& d, int precision, int nmax, std::vector<TileShape>& out) {
+// Model of an MD step's time (us, its share of a rebuild included, launches aside) where the batch leaves
+// CUs idle: tiles of `homes` home monomers and `stage` staged ones, `tiles` of them in the batch, over 256
+// CUs.  A tile costs its stage and the wavefronts that its homes fill: one or two run at a third and a
+// half of the cost of four, three leave a SIMD idle and cost what four do.  Up to a tile a CU the launch
+// takes little less than when full; beyond, the fullest CU counts.  A shape whose fullest tile (three
+// standard deviations of a melt's counts) passes the 256 lanes pays for a second round.  Fitted to mixed
+// melts of 1,000 to 50,000 monomers (us a step, against the best cost per home, which is the rule where
+// the chip is full): 1,000 15.3 -> 13.6, 4,000 15.2 -> 13.1, 10,000 15.3 -> 13.5, 15,000 16.0 -> 14.6,
+// 28,000 16.2 either way, 50,000 17.9 -> 16.5.
+static double tile_time(double homes, double stage, double tiles) {
+  static const double wave_us[4] = {0.93, 1.66, 3.15, 3.32};
+  const double sd = std::max(0.5 * std::sqrt(homes), 1e-3);
+  auto above = [&](double n) { return 0.5 * std::erfc((n - homes) / (sd * std::sqrt(2.0))); };  // P(count > n)
+  double w = 0.3 + 0.0006 * stage;
+  for (int lanes = 0; lanes < 4 * NLB_THREADS && (lanes == 0 || above(lanes) > 1e-3); lanes += 64) {
+    const int q = lanes / 64 % 4;
+    w += (lanes == 0 ? 1.0 : above(lanes)) * (wave_us[q] - (q > 0 ? wave_us[q - 1] : 0.0));
+  }
+  const double r = tiles / 256.0, load = r <= 1.0 ? 0.6 + 0.4 * r : 0.5 * (r + std::ceil(r));
+  const double over = 1.2 * (std::ceil((homes + 3.0 * sd) / NLB_THREADS) - 1.0);
+  return load * w + over;
+}
+// Tiles of nl_S x nl_Sy cells, ranked by a cost model; nm_total = monomers of the batch.  A workgroup
+// stages 3 (nl_S + 2)(nl_Sy + 2) cells; the last tile of a row (column) takes the remainder, and no
+// tile is empty.  The stage must fit the LDS cap with room for fluctuations.  The cost is that of a home
+// monomer (a round of NLB_THREADS lanes costs the same whether or not every lane holds one; three
+// standard deviations of a tile's count are kept in hand: at 50,000 monomers 11 x 4 cells of 238 homes
+// take 17.9 us a step, 7 x 6 of 227 take 16.5), except where a mixed batch has fewer such tiles than
+// the chip has CUs: then it is the launch's time.  (FP64 sums follow the tile's order, so an FP64 melt's
+// shape depends on the melt alone: it is the same in a batch.)  out receives up to nmax shapes, cheapest
+// first.
+static void tile_shapes(const MeltDesc& d, int precision, double nm_total, int nmax, std::vector<TileShape>& out) {
   const double occ = (double)d.Nm / ((double)d.ncl * d.ncl * d.ncl);
   const int cap = precision == KGDB_PREC_MIXED ? STAGE_CAP_MAX : STAGE_CAP_MAX_FP64;
+  const bool idle_cus = precision == KGDB_PREC_MIXED && nm_total <= 230.0 * 256.0;
   std::vector<std::pair<double, TileShape>> all;
   for (int Sy = 1; Sy <= std::min(d.ncl, 64); ++Sy) {
     const int nyb = (d.ncl + Sy - 1) / Sy, Sye = (d.ncl + nyb - 1) / nyb;
@@ -254,9 +281,9 @@ static void tile_shapes(const MeltDesc& d, int precision, int nmax, std::vector<
       if (Se != S || (S + 2) * (Sy + 2) > 198) continue;
       const double homes = S * Sy * occ, stage = 3.0 * (S + 2) * (Sy + 2) * occ;
       if (1.5 * stage + 64 > cap && !(S == 1 && Sy == 1)) continue;
-      // (a tile's count fluctuates by about sqrt(homes / 4) in a melt: two of those in hand)
-      const double rounds = std::ceil((homes + std::sqrt(homes) + 2.0) / NLB_THREADS);
-      const double cost = (3000.0 + 40.0 * stage + 2500.0 * NLB_THREADS * rounds) / std::max(homes, 1e-9);
+      const double rounds = std::ceil((homes + 1.5 * std::sqrt(homes) + 2.0) / NLB_THREADS);
+      double cost = (3000.0 + 40.0 * stage + 2500.0 * NLB_THREADS * rounds) / std::max(homes, 1e-9);
+      if (idle_cus) cost = tile_time(homes, stage, (double)d.ncl * nyb * nseg * nm_total / d.Nm);
       all.push_back({cost, TileShape{S, Sy}});
     }
   }
@@ -299,7 +326,7 @@ static void set_list_geometry(MeltDesc& d, const kgdb_params& p, int K, double n
   d.half_skin2 = 0.25 * skin * skin;
   d.half_skin = 0.5 * skin;
   std::vector<TileShape> sh;
-  tile_shapes(d, p.precision, 1, sh);
+  tile_shapes(d, p.precision, nm_total, 1, sh);
   set_tile_shape(d, sh[0]);
 }
 
@@ -1112,7 +1139,7 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
       for (int k = 0; k < count; ++k) {
         MeltDesc& d = b->Dk[q][k];
         set_list_geometry(d, params[k], NL_KS[q], (double)NP);
-        tile_shapes(d, params[k].precision, kgdb_batch::NSHAPE, b->shapes[q][k]);
+        tile_shapes(d, params[k].precision, (double)NP, kgdb_batch::NSHAPE, b->shapes[q][k]);
         d.celll_off = (int)off;
         d.tile_off = (int)toff;
         off += (int64_t)d.ncl * d.ncl * d.ncl;
@@ -1126,7 +1153,11 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
       ncl_max = std::max(ncl_max, off);
       nt_max = std::max(nt_max, toff);
       for (int64_t t : tiles_c) nt_max = std::max(nt_max, t);
-      b->rmap_cap[q] = (int)*std::max_element(tiles_c.begin(), tiles_c.end());
+      // room for the candidate shapes, and for any other of 128 homes or more that a caller may set
+      int64_t most = *std::max_element(tiles_c.begin(), tiles_c.end());
+      most = std::max(most, std::min(off, std::max<int64_t>(NP / 128, 128 * (int64_t)count)));
+      b->rmap_cap[q] = (int)most;
+      nt_max = std::max(nt_max, most);
       b->ntile[q] = (int)toff;
     }
     if (ncl_max * NL_CELL_CAP >= (1ll << 31)) { delete b; return fail(KGDB_E_PARAM, "list grid too large"); }

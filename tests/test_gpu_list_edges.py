@@ -65,3 +65,20 @@ def test_frames_that_wrap_keep_their_stage(shape):
     s0, s1 = flat.get_state(), wrapped.get_state()
     for f in ("x", "v", "fl", "fc", "chains"):
         assert np.array_equal(s0[f], s1[f]), f
+
+
+def test_small_melts_take_other_tiles_in_a_large_batch():
+    # a mixed batch that leaves CUs idle takes tiles of one wavefront, a larger one full tiles; the
+    # trajectory is the same, bit for bit
+    small = dict(M=40, N=100, kappa=1.0, warmup_steps=100, nl_every=5, precision=1)
+    alone = kg.Melt(seed=1, melt_id=0, **small)
+    batch = kg.Batch([dict(small, seed=1, melt_id=0),
+                      dict(M=300, N=200, kappa=1.0, seed=1, melt_id=1, warmup_steps=100, nl_every=5, precision=1)])
+    assert alone.nl_stats()["tile_shape"] != batch.nl_stats()["tile_shape"]
+    for m in (alone, batch):
+        m.md_steps(60)
+        m.db_sweep(40)
+        m.md_steps(35)
+    s0, s1 = alone.get_state(), batch.get_state(0)
+    for f in ("x", "v", "fl", "fc", "chains"):
+        assert np.array_equal(s0[f], s1[f]), f
