@@ -116,8 +116,8 @@ class Batch:
     def get_state(self, melt=0):
         M, N = self._MN(melt)
         Nm = M * N
-        x, v, fc, fl = (np.zeros((3, Nm)) for _ in range(4))
-        ch = np.zeros(Nm, np.int32); cnt = np.zeros(4, np.uint64)
+        x, v, fc, fl = (np.empty((3, Nm)) for _ in range(4))
+        ch = np.empty(Nm, np.int32); cnt = np.zeros(4, np.uint64)
         check(load().kgdb_get_state(self._h, melt, ptr(x), ptr(v), ptr(fc), ptr(fl), ptr(ch), ptr(cnt)))
         return dict(x=x, v=v, fc=fc, fl=fl, chains=ch.reshape(M, N), counters=cnt)
 

@@ -75,6 +75,14 @@ struct CopyJobs {
   int n;
 };
 bool launch_copy_jobs(const CopyJobs& c, hipStream_t s);
+// a melt's read-out: up to 12 slot-ordered components (each [NP]) and the chain table
+struct ReadArgs {
+  const double* comp[12];
+  const int *slot_of, *mono, *chain;
+  int ncomp, off, Nm;
+};
+void launch_slot_of_id(const int* mono, int off, int Nm, int* slot_of, hipStream_t s);
+void launch_read_by_id(const ReadArgs& a, uint32_t w0, uint32_t nw, uint64_t* out, hipStream_t s);
 size_t spos_bytes(int prec);
 
 // ---- neighbour-list MD step (kgdb_nl.hip)

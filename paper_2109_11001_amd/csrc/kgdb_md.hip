@@ -419,6 +419,34 @@ __global__ void k_fill_i32(int* p, int n, int v) {
   if (i < n) p[i] = v;
 }
 
+// storage slot of each monomer id of one melt
+__global__ __launch_bounds__(256) void k_slot_of_id(const int* __restrict__ mono, int off, int Nm,
+                                                    int* __restrict__ slot_of) {
+  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i >= Nm) return;
+  const int id = mono[off + i];
+  if (id >= 0 && id < Nm) slot_of[off + id] = off + i;
+}
+
+// Words w0 .. w0 + nw - 1 of a melt's read-out in id order: the components one after the other, then the
+// chain table as pairs of monomer ids.  A word is one random 8-byte read and a coalesced write; the copy
+// to the host that follows is ten times slower.
+__global__ __launch_bounds__(256) void k_read_by_id(ReadArgs a, uint32_t w0, uint32_t nw, uint64_t* __restrict__ out) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nw) return;
+  const uint32_t w = w0 + i, Nm = (uint32_t)a.Nm, nd = (uint32_t)a.ncomp * Nm;
+  if (w < nd) {
+    const uint32_t c = w / Nm, id = w - c * Nm;
+    const int slot = min(max(a.slot_of[a.off + id], a.off), a.off + a.Nm - 1);
+    out[i] = (uint64_t)__double_as_longlong(a.comp[c][slot]);
+  } else {
+    const uint32_t j = 2 * (w - nd);
+    auto id_at = [&](uint32_t q) { return (uint32_t)a.mono[min(max(a.chain[a.off + q], a.off), a.off + a.Nm - 1)]; };
+    const uint32_t lo = id_at(j), hi = j + 1 < Nm ? id_at(j + 1) : 0u;
+    out[i] = (uint64_t)hi << 32 | lo;
+  }
+}
+
 // several device-to-device copies in one launch (the state saved at the start of a pass and
 // restored on a rollback), grid-stride; a job whose addresses and size are multiples of 16
 // bytes moves 16-byte words, any other 4-byte words (every buffer here is a whole number of them)
@@ -495,6 +523,13 @@ void launch_advance(uint64_t* step_base, int nm, uint64_t n, hipStream_t s) {
 
 void launch_fill_i32(int* p, int n, int v, hipStream_t s) {
   if (n > 0) hipLaunchKernelGGL(k_fill_i32, dim3((n + 255) / 256), dim3(256), 0, s, p, n, v);
+}
+
+void launch_slot_of_id(const int* mono, int off, int Nm, int* slot_of, hipStream_t s) {
+  hipLaunchKernelGGL(k_slot_of_id, dim3((Nm + 255) / 256), dim3(256), 0, s, mono, off, Nm, slot_of);
+}
+void launch_read_by_id(const ReadArgs& a, uint32_t w0, uint32_t nw, uint64_t* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_read_by_id, dim3((nw + 255) / 256), dim3(256), 0, s, a, w0, nw, out);
 }
 
 bool launch_copy_jobs(const CopyJobs& c, hipStream_t s) {
