@@ -275,9 +275,10 @@ static double tile_time(double homes, double stage, double tiles) {
 // monomer (a round of NLB_THREADS lanes costs the same whether or not every lane holds one; three
 // standard deviations of a tile's count are kept in hand: at 50,000 monomers 11 x 4 cells of 238 homes
 // take 17.9 us a step, 7 x 6 of 227 take 16.5), except where a mixed batch has fewer such tiles than
-// the chip has CUs: then it is the launch's time.  (FP64 sums follow the tile's order, so an FP64 melt's
-// shape depends on the melt alone: it is the same in a batch.)  out receives up to nmax shapes, cheapest
-// first.
+// the chip has CUs: then it is the launch's time.  (FP64 sums follow the tile's order, so an
+// FP64 melt's shape depends on the melt alone, being the same in a batch, and keeps two deviations in
+// hand: few sizes gain by a third, and their trajectories would take another rounding.)  out receives up
+// to nmax shapes, cheapest first.
 static void tile_shapes(const MeltDesc& d, int precision, double nm_total, int nmax, std::vector<TileShape>& out) {
   const double occ = (double)d.Nm / ((double)d.ncl * d.ncl * d.ncl);
   const int cap = precision == KGDB_PREC_MIXED ? STAGE_CAP_MAX : STAGE_CAP_MAX_FP64;
@@ -291,7 +292,8 @@ static void tile_shapes(const MeltDesc& d, int precision, double nm_total, int n
       if (Se != S || (S + 2) * (Sy + 2) > 198) continue;
       const double homes = S * Sy * occ, stage = 3.0 * (S + 2) * (Sy + 2) * occ;
       if (1.5 * stage + 64 > cap && !(S == 1 && Sy == 1)) continue;
-      const double rounds = std::ceil((homes + 1.5 * std::sqrt(homes) + 2.0) / NLB_THREADS);
+      const double in_hand = (precision == KGDB_PREC_MIXED ? 1.5 : 1.0) * std::sqrt(homes);
+      const double rounds = std::ceil((homes + in_hand + 2.0) / NLB_THREADS);
       double cost = (3000.0 + 40.0 * stage + 2500.0 * NLB_THREADS * rounds) / std::max(homes, 1e-9);
       if (idle_cus) cost = tile_time(homes, stage, (double)d.ncl * nyb * nseg * nm_total / d.Nm);
       all.push_back({cost, TileShape{S, Sy}});
