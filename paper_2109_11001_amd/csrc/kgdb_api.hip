@@ -909,6 +909,8 @@ void kgdb_destroy(kgdb_batch* b) {
   delete b;
 }
 
+// members of 24 bytes that leave four steps' workgroups a CU's LDS
+static constexpr int STAGE_CAP_FP64_4 = 1472;
 // LDS stage of a tile: 1.5 x the largest mean neighbourhood of a tile + 64 (density
 // fluctuations of a melt that is still relaxing from its start are large), at most 2688
 // members (mixed) or 1792 (FP64), which keeps the step's and the rebuild's LDS within 64 KB;
@@ -921,7 +923,11 @@ static int stage_cap_for(const kgdb_batch* b, int q) {
     mx = std::max(mx, 3.0 * (d.nl_S + 2) * (d.nl_Sy + 2) * occ);
     if (d.test_flags & TF_NL_GLOBAL) return 0;
   }
-  return std::min(b->prec ? STAGE_CAP_MAX : STAGE_CAP_MAX_FP64, ((int)(1.5 * mx) + 64 + 63) / 64 * 64);
+  const int cap = std::min(b->prec ? STAGE_CAP_MAX : STAGE_CAP_MAX_FP64, ((int)(1.5 * mx) + 64 + 63) / 64 * 64);
+  // FP64: four workgroups on a CU rather than three, while a quarter of the stage stays in hand (an
+  // equilibrated melt's stages vary by 2%; one that outgrows its capacity raises it for the next pass)
+  if (!b->prec && cap > STAGE_CAP_FP64_4 && 1.25 * mx + 64 <= STAGE_CAP_FP64_4) return STAGE_CAP_FP64_4;
+  return cap;
 }
 
 // (melt, local tile) of every list-grid tile of interval q, in the current shapes

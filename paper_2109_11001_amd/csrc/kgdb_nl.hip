@@ -855,13 +855,21 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_step(NlArgs a) {
     }
   };
   const uint4* __restrict__ words = (const uint4*)a.nlist;
+  // FP64 with an integer n / 2: position, velocity and the first chain partner wait until the pair loop
+  // is over.  125 registers instead of 145 let four workgroups share a CU: the 1,020 tiles of 200,000
+  // monomers run at once instead of 768 and 252 (41.3 -> 35.9 us a step with rebuilds; 400,000 74.5 ->
+  // 68.1; up to 100,000, and from 700,000 on, where memory is the bound, within 1% of before).  With all
+  // four partners late 1M took 5% longer; a bound on the registers spills, and changes the sums' rounding.
+  constexpr bool late = sizeof(R) == 8 && NH > 0;
   auto load_home = [&](int g) {
     Home o;
     o.ri = rel[g];
     o.n = pairs_on ? a.nlen[g] : 0;
     o.nb = a.nb4[g];
-    o.x = a.x[g]; o.y = a.x[NP + g]; o.z = a.x[2 * NP + g];
-    o.vx = a.v[g]; o.vy = a.v[NP + g]; o.vz = a.v[2 * NP + g];
+    if (!late) {
+      o.x = a.x[g]; o.y = a.x[NP + g]; o.z = a.x[2 * NP + g];
+      o.vx = a.v[g]; o.vy = a.v[NP + g]; o.vz = a.v[2 * NP + g];
+    }
     o.w0 = words[nl_word(g, 0)];
     noise(o, (MODE & F_CLOSE) ? a.mono[g] : 0);
     return o;
@@ -958,7 +966,7 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_step(NlArgs a) {
     const P ri = hm.ri;
     const int n = hm.n;
     const int4 nb = hm.nb;
-    const double xg = hm.x, yg = hm.y, zg = hm.z;
+    double xg = hm.x, yg = hm.y, zg = hm.z;
     double vx = hm.vx, vy = hm.vy, vz = hm.vz;
     uint4 wd = hm.w0;
     const int pc = Rel<R>::cell(ri);
@@ -974,6 +982,7 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_step(NlArgs a) {
       // (a slot past the storage can only come from a rebuild that overflowed, whose run is redone)
       const bool on = forces_on && nbq[q] >= 0 && nbq[q] < NP;
       nbmask |= on ? 1u << q : 0u;
+      if (late && q == 0) continue;
       rb[q] = rel[on ? nbq[q] : g];
       rbc[q] = Rel<R>::cell(rb[q]);
     }
@@ -1047,6 +1056,10 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_step(NlArgs a) {
     }
     F.x *= u; F.y *= u; F.z *= u;  // coef * (x_j - x_i): units -> sigma
 
+    if (late) {
+      rb[0] = rel[nbmask & 1u ? nbq[0] : g];
+      rbc[0] = Rel<R>::cell(rb[0]);
+    }
     // bonded partners: displacement from the relative positions and the reference cells
     W3<R> Pd[5];
     bool has[5];
@@ -1118,6 +1131,7 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_step(NlArgs a) {
       }
     }
 
+    if (late) { vx = a.v[g]; vy = a.v[NP + g]; vz = a.v[2 * NP + g]; }
     const double Fx = (double)F.x, Fy = (double)F.y, Fz = (double)F.z;
     if (!(isfinite(Fx) && isfinite(Fy) && isfinite(Fz))) errbits |= ERR_NONFINITE;
     double fx, fy, fz;
@@ -1140,6 +1154,7 @@ __global__ __launch_bounds__(NLB_THREADS) void k_nl_step(NlArgs a) {
       if (!(isfinite(vx) && isfinite(vy) && isfinite(vz))) errbits |= ERR_NONFINITE;
     }
     if (MODE & F_OPEN) {
+      if (late) { xg = a.x[g]; yg = a.x[NP + g]; zg = a.x[2 * NP + g]; }
       const double hx = vx + 0.5 * dt * (Fx + fx);
       const double hy = vy + 0.5 * dt * (Fy + fy);
       const double hz = vz + 0.5 * dt * (Fz + fz);
