@@ -1173,9 +1173,9 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
       ncl_max = std::max(ncl_max, off);
       nt_max = std::max(nt_max, toff);
       for (int64_t t : tiles_c) nt_max = std::max(nt_max, t);
-      // room for the candidate shapes, and for any other of 128 homes or more that a caller may set
+      // room for the candidate shapes, and for others of 128 homes or more that a caller may set
       int64_t most = *std::max_element(tiles_c.begin(), tiles_c.end());
-      most = std::max(most, std::min(off, std::max<int64_t>(NP / 128, 128 * (int64_t)count)));
+      most = std::max(most, std::min(off, NP / 128 + 8 * (int64_t)count));
       b->rmap_cap[q] = (int)most;
       nt_max = std::max(nt_max, most);
       b->ntile[q] = (int)toff;

@@ -6,11 +6,12 @@
 // the tiles of a plane, then the planes, follow one another ("sorted cell index").
 //
 // Rebuild (every K steps).  (1) Binning: each monomer's list cell, counted per cell and per
-// tile (wave-aggregated atomics) with its storage slot appended to the cell's bucket; the
-// step before a rebuild bins the positions it has just written.  (2) A scan of the tile
-// counts gives each tile's first storage slot.  (3) One workgroup per tile stages the members
-// of the 3 (nl_S + 2)(nl_Sy + 2) cells around the tile in LDS, ordered by cell and by monomer
-// id within a cell, at their positions relative to the tile (so that periodic images need no
+// tile (wave-aggregated atomics) with its storage slot, id and place in the cell (16-bit units)
+// appended to the cell's bucket; the step before a rebuild bins the positions it has just
+// written.  (2) A scan of the tile counts gives each tile's first storage slot.  (3) One
+// workgroup per tile stages the members of the 3 (nl_S + 2)(nl_Sy + 2) cells around the tile
+// in LDS, ordered by cell and by monomer id within
+// a cell, at their places relative to the tile (so that periodic images need no
 // offsets); it moves its own members to their new storage slots (cell order, monomer id
 // within a cell: a canonical order that does not depend on the history of the run), records
 // each one's position relative to its cell (its reference cell until the next rebuild), and
