@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <initializer_list>
 #include <mutex>
 #include <string>
@@ -269,20 +270,14 @@ static double tile_time(double homes, double stage, double tiles) {
   const double over = 1.2 * (std::ceil((homes + 3.0 * sd) / NLB_THREADS) - 1.0);
   return load * w + over;
 }
-// Tiles of nl_S x nl_Sy cells, ranked by a cost model; nm_total = monomers of the batch.  A workgroup
-// stages 3 (nl_S + 2)(nl_Sy + 2) cells; the last tile of a row (column) takes the remainder, and no
-// tile is empty.  The stage must fit the LDS cap with room for fluctuations.  The cost is that of a home
-// monomer (a round of NLB_THREADS lanes costs the same whether or not every lane holds one; three
-// standard deviations of a tile's count are kept in hand: at 50,000 monomers 11 x 4 cells of 238 homes
-// take 17.9 us a step, 7 x 6 of 227 take 16.5), except where a mixed batch has fewer such tiles than
-// the chip has CUs: then it is the launch's time.  (FP64 sums follow the tile's order, so an
-// FP64 melt's shape depends on the melt alone, being the same in a batch, and keeps two deviations in
-// hand: few sizes gain by a third, and their trajectories would take another rounding.)  out receives up
-// to nmax shapes, cheapest first.
-static void tile_shapes(const MeltDesc& d, int precision, double nm_total, int nmax, std::vector<TileShape>& out) {
+// The tile shapes of nl_S x nl_Sy cells of melt d, by cost(shape, home monomers, staged monomers of a
+// tile): a workgroup stages 3 (nl_S + 2)(nl_Sy + 2) cells; the last tile of a row (column) takes the
+// remainder, and no tile is empty; the stage must fit the LDS cap with room for fluctuations.  out receives
+// up to nmax shapes, cheapest first.
+static void rank_shapes(const MeltDesc& d, int precision, const std::function<double(TileShape, double, double)>& cost,
+                        int nmax, std::vector<TileShape>& out) {
   const double occ = (double)d.Nm / ((double)d.ncl * d.ncl * d.ncl);
   const int cap = precision == KGDB_PREC_MIXED ? STAGE_CAP_MAX : STAGE_CAP_MAX_FP64;
-  const bool idle_cus = precision == KGDB_PREC_MIXED && nm_total <= 230.0 * 256.0;
   std::vector<std::pair<double, TileShape>> all;
   for (int Sy = 1; Sy <= std::min(d.ncl, 64); ++Sy) {
     const int nyb = (d.ncl + Sy - 1) / Sy, Sye = (d.ncl + nyb - 1) / nyb;
@@ -292,17 +287,35 @@ static void tile_shapes(const MeltDesc& d, int precision, double nm_total, int n
       if (Se != S || (S + 2) * (Sy + 2) > 198) continue;
       const double homes = S * Sy * occ, stage = 3.0 * (S + 2) * (Sy + 2) * occ;
       if (1.5 * stage + 64 > cap && !(S == 1 && Sy == 1)) continue;
-      const double in_hand = (precision == KGDB_PREC_MIXED ? 1.5 : 1.0) * std::sqrt(homes);
-      const double rounds = std::ceil((homes + in_hand + 2.0) / NLB_THREADS);
-      double cost = (3000.0 + 40.0 * stage + 2500.0 * NLB_THREADS * rounds) / std::max(homes, 1e-9);
-      if (idle_cus) cost = tile_time(homes, stage, (double)d.ncl * nyb * nseg * nm_total / d.Nm);
-      all.push_back({cost, TileShape{S, Sy}});
+      all.push_back({cost(TileShape{S, Sy}, homes, stage), TileShape{S, Sy}});
     }
   }
   std::stable_sort(all.begin(), all.end(), [](const auto& x, const auto& y) { return x.first < y.first; });
   out.clear();
   for (size_t i = 0; i < all.size() && (int)out.size() < nmax; ++i) out.push_back(all[i].second);
   if (out.empty()) out.push_back(TileShape{1, 1});
+}
+static int64_t tiles_of(const MeltDesc& d, TileShape t) {
+  return (int64_t)d.ncl * ((d.ncl + t.Sy - 1) / t.Sy) * ((d.ncl + t.S - 1) / t.S);
+}
+// cost of a home monomer with `sd` standard deviations of a tile's count in hand
+static double home_cost(double homes, double stage, double sd) {
+  const double rounds = std::ceil((homes + 0.5 * sd * std::sqrt(homes) + 2.0) / NLB_THREADS);
+  return (3000.0 + 40.0 * stage + 2500.0 * NLB_THREADS * rounds) / std::max(homes, 1e-9);
+}
+// Tile shapes of melt d, nm_total = monomers of the batch.  The cost is that of a home monomer (a round of
+// NLB_THREADS lanes costs the same whether or not every lane holds one; three standard deviations of a
+// tile's count are kept in hand: at 50,000 monomers 11 x 4 cells of 238 homes take 17.9 us a step, 7 x 6 of
+// 227 take 16.5), except where a mixed batch has fewer such tiles than the chip has CUs: then it is the
+// launch's time.  (FP64 sums follow the tile's order, so an FP64 melt's shape depends on the melt alone,
+// being the same in a batch, and keeps two deviations in hand: few sizes gain by a third, and their
+// trajectories would take another rounding.)
+static void tile_shapes(const MeltDesc& d, int precision, double nm_total, int nmax, std::vector<TileShape>& out) {
+  const bool idle_cus = precision == KGDB_PREC_MIXED && nm_total <= 230.0 * 256.0;
+  rank_shapes(d, precision, [&](TileShape t, double homes, double stage) {
+    if (idle_cus) return tile_time(homes, stage, (double)tiles_of(d, t) * nm_total / d.Nm);
+    return home_cost(homes, stage, precision == KGDB_PREC_MIXED ? 3.0 : 2.0);
+  }, nmax, out);
 }
 static void set_tile_shape(MeltDesc& d, TileShape t) {
   d.nl_S = t.S;
@@ -322,7 +335,10 @@ static bool tile_shape_ok(const MeltDesc& d, int precision, TileShape t) {
   return 1.5 * 3.0 * (t.S + 2) * (t.Sy + 2) * occ + 64 <= cap;
 }
 
-static void set_list_geometry(MeltDesc& d, const kgdb_params& p, int K, double nm_total) {
+// list grid of interval K in a batch of nm_total monomers, with the cheapest of its tile shapes; shapes
+// receives the nmax cheapest
+static void set_list_geometry(MeltDesc& d, const kgdb_params& p, int K, double nm_total, int nmax,
+                              std::vector<TileShape>& shapes) {
   const double rc = std::pow(2.0, 1.0 / 6.0);
   const double skin = nl_skin_for(p, K, nm_total);
   const double rl = rc + skin;
@@ -337,9 +353,8 @@ static void set_list_geometry(MeltDesc& d, const kgdb_params& p, int K, double n
   d.nl_wide = (double)d.Nm / ((double)d.ncl * d.ncl * d.ncl) > 6.5 ? 1 : 0;
   d.half_skin2 = 0.25 * skin * skin;
   d.half_skin = 0.5 * skin;
-  std::vector<TileShape> sh;
-  tile_shapes(d, p.precision, nm_total, 1, sh);
-  set_tile_shape(d, sh[0]);
+  tile_shapes(d, p.precision, nm_total, nmax, shapes);
+  set_tile_shape(d, shapes[0]);
 }
 
 static MeltDesc make_desc(const kgdb_params& p) {
@@ -369,7 +384,8 @@ static MeltDesc make_desc(const kgdb_params& p) {
   d.inv_mnb = 1.0 / ((double)d.M * (double)(d.N - 1));
   d.inv_nb = 1.0 / (double)(d.N - 1);
   d.lang_amp = std::sqrt(2.0 * p.gamma * p.T / p.dt);
-  set_list_geometry(d, p, p.nl_every > 0 ? p.nl_every : 5, (double)d.Nm);
+  std::vector<TileShape> sh;
+  set_list_geometry(d, p, p.nl_every > 0 ? p.nl_every : 5, (double)d.Nm, 1, sh);
   d.seed = p.seed;
   d.melt_id = (uint64_t)(int64_t)p.melt_id;
   d.init_mode = p.init_mode;
@@ -1155,25 +1171,31 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
       int64_t off = 0, toff = 0;
       usable[q] = true;
       b->shapes[q].assign(count, {});
-      std::vector<int64_t> tiles_c(kgdb_batch::NSHAPE, 0);
+      // tiles of the batch when each melt takes its c-th candidate shape, and its c-th by the cost of a home
+      // monomer with two deviations in hand
+      std::vector<int64_t> tiles_c(2 * kgdb_batch::NSHAPE, 0);
       for (int k = 0; k < count; ++k) {
         MeltDesc& d = b->Dk[q][k];
-        set_list_geometry(d, params[k], NL_KS[q], (double)NP);
-        tile_shapes(d, params[k].precision, (double)NP, kgdb_batch::NSHAPE, b->shapes[q][k]);
+        set_list_geometry(d, params[k], NL_KS[q], (double)NP, kgdb_batch::NSHAPE, b->shapes[q][k]);
         d.celll_off = (int)off;
         d.tile_off = (int)toff;
         off += (int64_t)d.ncl * d.ncl * d.ncl;
         toff += (int64_t)d.ncl * d.nl_nyb * d.nl_nseg;
-        for (int c = 0; c < kgdb_batch::NSHAPE; ++c) {
-          const TileShape t = b->shapes[q][k][std::min<size_t>(c, b->shapes[q][k].size() - 1)];
-          tiles_c[c] += (int64_t)d.ncl * ((d.ncl + t.Sy - 1) / t.Sy) * ((d.ncl + t.S - 1) / t.S);
+        std::vector<TileShape> by_home;
+        rank_shapes(d, params[k].precision, [](TileShape, double homes, double stage) { return home_cost(homes, stage, 2.0); },
+                    kgdb_batch::NSHAPE, by_home);
+        const std::vector<TileShape>* lists[2] = {&b->shapes[q][k], &by_home};
+        for (int c = 0; c < 2 * kgdb_batch::NSHAPE; ++c) {
+          const auto& v = *lists[c / kgdb_batch::NSHAPE];
+          tiles_c[c] += tiles_of(d, v[std::min<size_t>(c % kgdb_batch::NSHAPE, v.size() - 1)]);
         }
         if (d.ncl < 3 || d.ncl > 1023) usable[q] = false;
       }
       ncl_max = std::max(ncl_max, off);
       nt_max = std::max(nt_max, toff);
-      for (int64_t t : tiles_c) nt_max = std::max(nt_max, t);
-      // room for the candidate shapes, and for others of 128 homes or more that a caller may set
+      // Tiles that a caller may set: as many as the costliest of those candidates needs, and at least one
+      // per 128 monomers and 8 a melt.  (The candidates by the launch's time alone left out shapes that a
+      // batch of few melts could always take: 15 x 9 cells at 50,000 monomers of density 0.1 and K = 2.)
       int64_t most = *std::max_element(tiles_c.begin(), tiles_c.end());
       most = std::max(most, std::min(off, NP / 128 + 8 * (int64_t)count));
       b->rmap_cap[q] = (int)most;
@@ -2071,7 +2093,7 @@ int kgdb_set_tiles(kgdb_batch* b, int32_t S, int32_t Sy) {
     int64_t n = 0;
     for (int k = 0; k < b->nm; ++k) {
       const MeltDesc& d = b->Dk[b->nl_ki][k];
-      n += (int64_t)d.ncl * ((d.ncl + Sy - 1) / Sy) * ((d.ncl + S - 1) / S);
+      n += tiles_of(d, TileShape{S, Sy});
     }
     return (int)std::min<int64_t>(n, 1ll << 30);
   }();

@@ -82,3 +82,16 @@ def test_small_melts_take_other_tiles_in_a_large_batch():
     s0, s1 = alone.get_state(), batch.get_state(0)
     for f in ("x", "v", "fl", "fc", "chains"):
         assert np.array_equal(s0[f], s1[f]), f
+
+
+@pytest.mark.parametrize("melts,kw,shapes", [
+    (1, dict(M=500, N=100, rho=0.1, nl_every=2), [(15, 9), (9, 15)]),
+    (3, dict(M=80, N=100, rho=0.85, dt=0.02, nl_every=5), [(3, 3)]),
+    (3, dict(M=100, N=100, rho=0.85, dt=0.02, nl_every=5), [(2, 5), (5, 2)]),
+])
+def test_shapes_of_the_home_cost_fit_the_tile_map(melts, kw, shapes):
+    # shapes among the three cheapest by the cost of a home monomer, whatever the batch's own candidates are
+    b = kg.Batch([dict(kw, seed=2, melt_id=i, warmup_steps=0, precision=1) for i in range(melts)])
+    for s in shapes:
+        b.set_tiles(*s)
+        assert b.nl_stats()["tile_shape"] == s
