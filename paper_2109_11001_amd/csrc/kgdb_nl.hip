@@ -33,6 +33,7 @@
 
 #include "kgdb_dev.h"
 #include "kgdb_kernels.h"
+#include "kgdb_list_run.h"
 
 namespace kgdb {
 
@@ -448,20 +449,20 @@ __device__ __forceinline__ int nl_list_one(const NlArgs& a, const ListArgs& l, i
     while (mask) {
       const int u = __builtin_clz(mask), v = 31 - __builtin_ctz(mask);
       e -= 2;
-      *(uint16_t*)f = (uint16_t)(b[r] + u);
-      *(uint16_t*)e = (uint16_t)(b[r] + v);
+      run_put(f, b[r] + u);
+      run_put(e, b[r] + v);
       f += 2;
       mask &= ~((0x80000000u >> u) | (0x80000000u >> v));
     }
   }
   const int words = (cnt + 7) >> 3;
-  for (int c = cnt; c < 8 * words; ++c) *(uint16_t*)(buf + 2 * c) = (uint16_t)l.pad;
+  for (int c = cnt; c < 8 * words; ++c) run_put(buf + 2 * c, l.pad);
   uint4* __restrict__ out = (uint4*)a.nlist + nl_word(g, 0);
 #pragma unroll
   for (int w = 0; w < LB_CAP / 8; ++w)
     if (w < words) {
-      const uint32_t* p = (const uint32_t*)(buf + 16 * w);
-      out[w * 64] = make_uint4(p[0], p[1], p[2], p[3]);
+      const unsigned char* p = buf + 16 * w;
+      out[w * 64] = make_uint4(run_word(p), run_word(p + 4), run_word(p + 8), run_word(p + 12));
     }
   return cnt;
 }
