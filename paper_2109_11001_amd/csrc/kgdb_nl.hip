@@ -432,8 +432,8 @@ __device__ __forceinline__ int nl_list_one(const NlArgs& a, const ListArgs& l, i
       mask |= more;
     }
     // none past the row, nor the monomer itself
-    mask = n[r] > 0 ? mask & (0xffffffffu << (32 - n[r])) : 0u;
-    if (r == 4) mask &= ~(0x80000000u >> (tme - b[r]));
+    mask = row_first(mask, n[r]);
+    if (r == 4) mask = row_without(mask, tme - b[r]);
     m[r] = mask;
     cnt += __popc(mask);
   }
