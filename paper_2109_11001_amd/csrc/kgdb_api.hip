@@ -1141,7 +1141,7 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
   b->nm = count;
   b->P.assign(params, params + count);
   b->prec = params[0].precision;
-  int64_t NP = 0, NC = 0, NC13 = 0;
+  int64_t NP = 0, NC = 0, NC13 = 0, neblk = 0;
   for (int k = 0; k < count; ++k) {
     MeltDesc d = make_desc(params[k]);
     if (d.nc < 3) { delete b; return fail(KGDB_E_PARAM, "box smaller than 3 cells per side"); }
@@ -1149,7 +1149,9 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
     d.off = (int)NP;
     d.cell_off = (int)NC;
     d.cell13_off = (int)NC13;
+    d.eblk_off = (int)neblk;
     NP += d.Nm;
+    neblk += (d.Nm + 255) / 256;
     NC += (int64_t)d.nc * d.nc * d.nc;
     NC13 += (int64_t)d.nc13 * d.nc13 * d.nc13;
     b->max_M = std::max(b->max_M, d.M);
@@ -1294,11 +1296,7 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
   step(dalloc(b, &b->d_step, (size_t)count));
   step(dalloc(b, &b->d_err, (size_t)count));
   step(dalloc(b, &b->d_out4, 4 * (size_t)count));
-  {
-    size_t nblk = 0;
-    for (const MeltDesc& d : b->D) nblk += (size_t)(d.Nm + 255) / 256;
-    step(dalloc(b, &b->d_epart, nblk));
-  }
+  step(dalloc(b, &b->d_epart, (size_t)neblk));
   step(dalloc(b, &b->d_cnt13, (size_t)NC13));
   step(dalloc(b, &b->d_bucket13, (size_t)NC13 * DB_CELL_CAP));
   step(dalloc(b, &b->d_nnb, np));

@@ -130,7 +130,9 @@ __global__ __launch_bounds__(256) void k_remove_mean(const MeltDesc* __restrict_
 
 // {U_pair, U_bond, U_ang, K} of 256 monomers, then of each melt from its blocks' sums (both in a
 // fixed order).  One workgroup per melt summing everything waited on memory at every turn: 1650 us
-// at 400,000 monomers against 13 us for the two launches.
+// at 400,000 monomers against 13 us for the two launches.  (A melt's first block stands in its descriptor:
+// counted up from the first melt by every workgroup, the energies of 2,048 melts of 200 monomers took 692 us
+// against 293.)
 __global__ __launch_bounds__(256) void k_reduce_blocks(const MeltDesc* __restrict__ md, const int* __restrict__ blk_melt,
                                                        const int* __restrict__ blk_base, int NP,
                                                        const double* __restrict__ outE, const double* __restrict__ v,
@@ -162,9 +164,7 @@ __global__ __launch_bounds__(256) void k_reduce_blocks(const MeltDesc* __restric
 __global__ __launch_bounds__(256) void k_reduce_melt(const MeltDesc* __restrict__ md, const double4* __restrict__ part,
                                                      double* __restrict__ out4) {
   __shared__ double s[256];
-  int b0 = 0;
-  for (int k = 0; k < (int)blockIdx.x; ++k) b0 += (md[k].Nm + 255) / 256;
-  const int b1 = b0 + (md[blockIdx.x].Nm + 255) / 256;
+  const int b0 = md[blockIdx.x].eblk_off, b1 = b0 + (md[blockIdx.x].Nm + 255) / 256;
   double4 acc = make_double4(0.0, 0.0, 0.0, 0.0);
   for (int i = b0 + (int)threadIdx.x; i < b1; i += 256) {
     const double4 p = part[i];
@@ -577,8 +577,9 @@ void launch_remove_mean(const MeltDesc* md, int nm, int NP, double* v, hipStream
 }
 void launch_reduce_melt(const MeltDesc* md, int nm, const BlockMap& pm, int NP, const double* outE, const double* v,
                         double4* part, double* out4, hipStream_t s) {
+  if (pm.nblk == nm) part = (double4*)out4;  // melts of one block: its sums are the melt's
   hipLaunchKernelGGL(k_reduce_blocks, dim3(pm.nblk), dim3(256), 0, s, md, pm.melt, pm.base, NP, outE, v, part);
-  hipLaunchKernelGGL(k_reduce_melt, dim3(nm), dim3(256), 0, s, md, part, out4);
+  if (pm.nblk != nm) hipLaunchKernelGGL(k_reduce_melt, dim3(nm), dim3(256), 0, s, md, part, out4);
 }
 void launch_prefix(const MeltDesc* md, int k, int M, int NP, const double* x, const int* chain, double* spre,
                    double* blen, hipStream_t s) {

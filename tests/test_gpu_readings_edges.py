@@ -2,6 +2,8 @@
 the box, whose staged batch is too dense to fit at once, or whose bins fill the LDS histogram; S(q)
 of one vector and of a remainder of 64; chains at the edges of the 256-bond pass; energies of melts
 that end inside a block of 256 monomers."""
+import time
+
 import numpy as np
 import pytest
 
@@ -71,3 +73,28 @@ def test_observables_and_energy_edges(kw):
     assert np.all(np.abs(r2g - r2o) <= 2 * terms * 2.0 ** -53 * r2o + 1e-300)
     assert bg == pytest.approx(bo, rel=M * N * 2.0 ** -52)
     assert np.allclose(gm.energy(), om.energy(), rtol=1e-12, atol=0)
+
+
+def test_energies_of_many_small_melts():
+    # one block a melt, several a melt and both: each melt's energies are those of the melt alone, bit for bit
+    for sizes in ([(4, 50)] * 5, [(4, 50), (9, 57), (8, 32), (5, 200), (4, 64)]):
+        kw = [dict(M=M, N=N, kappa=1.0, seed=5, melt_id=i, warmup_steps=50) for i, (M, N) in enumerate(sizes)]
+        b = kg.Batch(kw)
+        for k, p in enumerate(kw):
+            assert np.array_equal(b.energy(k), kg.Melt(**p).energy())
+
+
+def test_energy_time_does_not_grow_with_the_number_of_melts():
+    # 2,048 melts of 200 monomers against one of as many: the same work (the same time here; 2.5 times as long
+    # when each melt's sum counts the melts before it)
+    def best(b):
+        t = []
+        for _ in range(12):
+            t0 = time.perf_counter()
+            b.energy(b.nm - 1)
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    many = kg.Batch([dict(M=8, N=25, seed=5, melt_id=i, warmup_steps=50, precision=1) for i in range(2048)])
+    one = kg.Melt(M=2048, N=200, seed=5, warmup_steps=50, precision=1)
+    assert best(many) < 1.6 * best(one)
