@@ -262,17 +262,16 @@ __global__ __launch_bounds__(256) void k_r2(int M, int N, const double* __restri
 // width r_max / nbins.  Counts are integers, so the histogram is exact.
 //
 // A workgroup takes the monomers of PH_B^3 MD cells against those of the cells within R of them
-// (2 R + 1 <= nc), staged in LDS about a thousand at a time: every thread holds two of these and
-// runs over the home monomers.  Testing all pairs of a tile costs three times the distances that a
+// (2 R + 1 <= nc), staged in LDS up to 1,536 at a time (the cells of a batch are cut where that is
+// reached): every thread holds two of these and runs over the home monomers.  Testing all pairs of a tile costs three times the distances that a
 // search cell by cell would need, but no gather, cell arithmetic or division per pair.  Bound by
 // VALU issue (the binning of a hit, which some lane of a wavefront nearly always has).  400,000
 // monomers to 3 sigma: 5.8 ms (a thread per monomer, gathers from L2) against 0.91 ms.
 constexpr int PH_B = 4;
 constexpr int PH_CELLS = 1024;  // cells per staged batch
 constexpr int PH_CAP = 1536;    // staged monomers
-constexpr int PH_PIECE = 32;    // cells of a batch staged at once when all of it does not fit
 constexpr int PH_HOMES = 256;   // home monomers per round
-static_assert(PH_PIECE * CELL_CAP <= PH_CAP, "a piece always fits");
+static_assert(CELL_CAP <= PH_CAP, "a cell always fits");
 
 __global__ __launch_bounds__(256) void k_pair_hist(const MeltDesc* __restrict__ md, int k, int NP,
                                                    const double* __restrict__ x, const int* __restrict__ cnt,
@@ -360,15 +359,28 @@ __global__ __launch_bounds__(256) void k_pair_hist(const MeltDesc* __restrict__ 
       if (t == 255) s_pre[PH_CELLS] = at;
       __syncthreads();
       const int all = s_pre[PH_CELLS];
-      const int piece = all <= PH_CAP ? PH_CELLS : PH_PIECE;
-      for (int p0 = 0; p0 < nb_cells; p0 += piece) {
-        const int first = s_pre[p0], m = s_pre[min(p0 + piece, PH_CELLS)] - first;
+      for (int p0 = 0, p1; p0 < nb_cells; p0 = p1) {
+        // cells [p0, p1): as many as fit
+        const int first = s_pre[p0];
+        p1 = PH_CELLS;
+        if (all - first > PH_CAP) {
+          int lo = p0 + 1;
+          while (p1 - lo > 1) {
+            const int mid = (lo + p1) >> 1;
+            if (s_pre[mid] - first <= PH_CAP) lo = mid;
+            else p1 = mid;
+          }
+          p1 = lo;
+        }
+        const int m = s_pre[p1] - first;
         // where each staged monomer sits in the buckets, then its position
-        if (t * (PH_CELLS / 256) >= p0 && t * (PH_CELLS / 256) < p0 + piece) {
-          int a = at0 - first;
+        int a = at0 - first;
 #pragma unroll
-          for (int q = 0; q < PH_CELLS / 256; ++q)
-            for (int j = 0; j < n[q]; ++j) s_id[a++] = cell[q] * CELL_CAP + j;
+        for (int q = 0; q < PH_CELLS / 256; ++q) {
+          const int c = t * (PH_CELLS / 256) + q;
+          if (c >= p0 && c < p1)
+            for (int j = 0; j < n[q]; ++j) s_id[a + j] = cell[q] * CELL_CAP + j;
+          a += n[q];
         }
         __syncthreads();
         for (int j = t; j < m; j += 256) {

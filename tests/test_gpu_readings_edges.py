@@ -52,6 +52,31 @@ def test_pair_histogram_of_a_dense_half():
     assert np.array_equal(counts, om.pair_hist(4.0, 64))
 
 
+@pytest.mark.parametrize("kw,r_max", [
+    (dict(M=40, N=100, rho=1.3), 3.0),   # 2 a cell: a batch of 10^3 cells is cut once
+    (dict(M=40, N=100, rho=3.0), 3.5),   # 4 a cell, and batches cut into several pieces
+    (dict(M=31, N=97, rho=1.08), 4.1),   # a batch that ends near the cut
+])
+def test_pair_histogram_of_dense_melts(kw, r_max):
+    om, gm = pair(warmup_steps=100, seed=11, **kw)
+    counts, _ = gm.pair_correlation(r_max, 70)
+    assert np.array_equal(counts, om.pair_hist(r_max, 70))
+
+
+def test_pair_histogram_time_grows_with_the_density():
+    # 4,000 monomers at density 1.2 against 1.0: the same tiles hold a fifth more each, 1.44 times the pairs of
+    # a tile (7.8 times as long when a batch past the LDS was cut into pieces of 32 cells)
+    t = []
+    for rho in (1.0, 1.2):
+        m = kg.Melt(M=80, N=50, rho=rho, kappa=1.0, seed=3, warmup_steps=300, precision=1)
+        t.append(1e9)
+        for _ in range(10):
+            t0 = time.perf_counter()
+            m.pair_correlation(3.0, 150)
+            t[-1] = min(t[-1], time.perf_counter() - t0)
+    assert t[1] < 3 * t[0]
+
+
 @pytest.mark.parametrize("nq", [1, 63, 65])
 def test_structure_factor_of_few_vectors(nq):
     om, gm = pair(M=7, N=33, seed=8, warmup_steps=50)
