@@ -15,8 +15,7 @@ __host__ __device__ __forceinline__ void run_put(unsigned char* p, int v) { *(Ru
 __host__ __device__ __forceinline__ uint32_t run_word(const unsigned char* p) { return *(const RunWord*)p; }
 
 // A row's mask, candidate u in bit 31 - u, with the first n candidates; and without candidate u.  A row may be
-// longer than a mask (its list is then built entry by entry, once the rows' lengths are known): defined for
-// every n and u.
+// longer than a mask (its further candidates are tested one by one): defined for every n and u.
 __host__ __device__ __forceinline__ uint32_t row_first(uint32_t mask, int n) {
   return n > 0 ? mask & (0xffffffffu << (32 - (n < 32 ? n : 32))) : 0u;
 }

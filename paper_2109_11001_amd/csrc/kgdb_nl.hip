@@ -354,7 +354,11 @@ __device__ __forceinline__ uint2 quant_pos(int4 e, int i, int yy, int zz, int U)
 // entry (a list takes a seventh of its candidates), and all rows' bounds, then a row's candidates, are
 // requested before any is used.  The set bits then go to the thread's run in LDS, a row's first and last
 // ones at a time (its count of bits says where its entries end), and the list leaves as whole 16-byte
-// words.  A list of more than LB_CAP entries (it holds 19 on average) is stored entry by entry instead.
+// words.  Where a list of the wavefront has more than LB_CAP entries (it holds 19 on average at the usual
+// density, temperature and step) or a row more than 32 candidates, entries go in one at a time: those past
+// the run straight to the list, those of candidates past the mask after a test each.  (Such lists were built
+// a second time from the start: 50,000 mixed monomers took 26.3 us a step at density 1.3 and at T = 2, now
+// 19.7 and 20.8; at 0.85 and T = 1 16.7.)
 // Entry j of slot g lies in word nl_word(g, j / 8) at place j % 8; the last word is filled up with
 // `pad`, the index one past the stage, where the step keeps a position outside every cutoff: the step
 // reads whole words without testing the list's end.
@@ -379,7 +383,7 @@ __device__ __forceinline__ void list_row(const ListArgs& l, uint2 me, int ih, in
   bi = c0 + (dxl * dxl + e2 > l.rskip2 ? 1 : 0);
   ei = e2 > l.rskip2 ? bi : c0 + (dxr * dxr + e2 > l.rskip2 ? 2 : 3);
 }
-// the list entry by entry, members through at(t)
+// the list entry by entry, members through at(t) (a stage read from global memory)
 template <typename At>
 __device__ __forceinline__ int nl_list_any(const NlArgs& a, const ListArgs& l, int g, uint2 me, int tme, int ih, int yy, At at) {
   uint16_t* __restrict__ out = (uint16_t*)a.nlist + nl_word(g, 0) * 8;
@@ -437,26 +441,52 @@ __device__ __forceinline__ int nl_list_one(const NlArgs& a, const ListArgs& l, i
     m[r] = mask;
     cnt += __popc(mask);
   }
-  if (cnt > LB_CAP || nmax > 32)
-    return nl_list_any(a, l, g, me, tme, ih, yy, [&](int t) { return s_pos[t]; });
   unsigned char* const buf = s_list + threadIdx.x * LB_STRIDE;
-  unsigned char* front = buf;
+  if (__ballot(cnt > LB_CAP || nmax > 32)) {
+    // some lane's list is longer than its run, or a row longer than a mask: what lies past them goes to the
+    // list entry by entry
+    uint16_t* __restrict__ o16 = (uint16_t*)a.nlist + nl_word(g, 0) * 8;
+    auto put = [&](int j, int v) {
+      if (j < LB_CAP) run_put(buf + 2 * j, v);
+      else if (j < NL_CAP) o16[(j >> 3) * 512 + (j & 7)] = (uint16_t)v;
+    };
+    int j = 0;
 #pragma unroll
-  for (int r = 0; r < 9; ++r) {
-    uint32_t mask = m[r];
-    unsigned char *f = front, *e = front + 2 * __popc(mask);
-    front = e;
-    while (mask) {
-      const int u = __builtin_clz(mask), v = 31 - __builtin_ctz(mask);
-      e -= 2;
-      run_put(f, b[r] + u);
-      run_put(e, b[r] + v);
-      f += 2;
-      mask &= ~((0x80000000u >> u) | (0x80000000u >> v));
+    for (int r = 0; r < 9; ++r) {
+      for (uint32_t mask = m[r]; mask; ++j) {
+        const int u = __builtin_clz(mask);
+        put(j, b[r] + u);
+        mask &= ~(0x80000000u >> u);
+      }
+      if (nmax > 32) {
+        int bi, ei;
+        list_row(l, me, ih, yy, r, bi, ei);
+        const int e = l.s_off[ei];
+        for (int t = b[r] + 32; t < e; ++t)
+          if (t != tme && quant_test(s_pos[t], me, l.minus_r2) < 0) put(j++, t);
+      }
     }
+    cnt = j;
+    for (int c = cnt; c & 7; ++c) put(c, l.pad);
+  } else {
+    unsigned char* front = buf;
+#pragma unroll
+    for (int r = 0; r < 9; ++r) {
+      uint32_t mask = m[r];
+      unsigned char *f = front, *e = front + 2 * __popc(mask);
+      front = e;
+      while (mask) {
+        const int u = __builtin_clz(mask), v = 31 - __builtin_ctz(mask);
+        e -= 2;
+        run_put(f, b[r] + u);
+        run_put(e, b[r] + v);
+        f += 2;
+        mask &= ~((0x80000000u >> u) | (0x80000000u >> v));
+      }
+    }
+    for (int c = cnt; c & 7; ++c) run_put(buf + 2 * c, l.pad);
   }
   const int words = (cnt + 7) >> 3;
-  for (int c = cnt; c < 8 * words; ++c) run_put(buf + 2 * c, l.pad);
   uint4* __restrict__ out = (uint4*)a.nlist + nl_word(g, 0);
 #pragma unroll
   for (int w = 0; w < LB_CAP / 8; ++w)

@@ -2,6 +2,8 @@
 rows of more candidates than one (20) or two (32) tests at once take, lists longer than a thread's run
 in LDS (32), frames that wrap onto themselves, a tile remainder of one cell.  FP64 steps against the
 oracle, and the mixed path's staged build against its build from global memory."""
+import time
+
 import numpy as np
 import pytest
 
@@ -22,6 +24,7 @@ CASES = [
     dict(M=40, N=100, rho=1.3),   # rows of 24, lists of 29: some past 32
     dict(M=100, N=100, rho=0.85),  # five a cell (groups of 8, some cells past it)
     dict(M=37, N=61, rho=0.6),
+    dict(M=64, N=100, rho=1.5),   # rows and lists on both sides of 32, in the same wavefronts
 ]
 
 
@@ -95,3 +98,19 @@ def test_shapes_of_the_home_cost_fit_the_tile_map(melts, kw, shapes):
     for s in shapes:
         b.set_tiles(*s)
         assert b.nl_stats()["tile_shape"] == s
+
+
+def test_step_time_of_long_lists():
+    # 50,000 monomers at T = 2, whose lists hold 30 entries (a wider skin) instead of 19: 1.24 times the step
+    # time of T = 1 (1.57 times when lists past the run were built a second time)
+    t = []
+    for T in (1.0, 2.0):
+        m = kg.Melt(M=250, N=200, kappa=1.0, T=T, seed=3, warmup_steps=500, precision=1, nl_every=5)
+        m.md_steps(400)
+        t.append(1e9)
+        for _ in range(12):
+            t0 = time.perf_counter()
+            m.md_steps(200)
+            t[-1] = min(t[-1], time.perf_counter() - t0)
+        assert m.nl_info()["K"] == 5
+    assert t[1] < 1.42 * t[0]
