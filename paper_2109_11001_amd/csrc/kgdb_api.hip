@@ -306,16 +306,28 @@ static double home_cost(double homes, double stage, double sd) {
 // Tile shapes of melt d, nm_total = monomers of the batch.  The cost is that of a home monomer (a round of
 // NLB_THREADS lanes costs the same whether or not every lane holds one; three standard deviations of a
 // tile's count are kept in hand: at 50,000 monomers 11 x 4 cells of 238 homes take 17.9 us a step, 7 x 6 of
-// 227 take 16.5), except where a mixed batch has fewer such tiles than the chip has CUs: then it is the
-// launch's time.  (FP64 sums follow the tile's order, so an FP64 melt's shape depends on the melt alone,
-// being the same in a batch, and keeps two deviations in hand: few sizes gain by a third, and their
-// trajectories would take another rounding.)
+// 227 take 16.5; at 200,000 and T = 2 8 x 4 of 237 take 40.5, 6 x 5 of 222 36.3), except where a mixed batch
+// has fewer such tiles than the chip has CUs: then it is the launch's time.  Two deviations are kept in hand
+// where three take the batch past the tiles that run at once, four a CU, and two do not: a few tiles with a
+// second round cost less than a few tiles left over (200,000 at K = 2: 880 tiles of 11 x 9 cells and 232
+// homes 45.2 us a step, 1,056 of 15 x 6 and 211 homes 55.5).  (FP64 sums follow the tile's order, so an FP64
+// melt's shape depends on the melt alone, being the same in a batch, and keeps two deviations in hand: few
+// sizes gain by a third, and their trajectories would take another rounding.)
 static void tile_shapes(const MeltDesc& d, int precision, double nm_total, int nmax, std::vector<TileShape>& out) {
-  const bool idle_cus = precision == KGDB_PREC_MIXED && nm_total <= 230.0 * 256.0;
-  rank_shapes(d, precision, [&](TileShape t, double homes, double stage) {
-    if (idle_cus) return tile_time(homes, stage, (double)tiles_of(d, t) * nm_total / d.Nm);
-    return home_cost(homes, stage, precision == KGDB_PREC_MIXED ? 3.0 : 2.0);
-  }, nmax, out);
+  const double per_tile = nm_total / d.Nm, at_once = 4.0 * 256.0;
+  auto by_home = [&](double sd) {
+    rank_shapes(d, precision, [sd](TileShape, double homes, double stage) { return home_cost(homes, stage, sd); }, nmax, out);
+    return (double)tiles_of(d, out[0]) * per_tile;
+  };
+  if (precision != KGDB_PREC_MIXED) {
+    by_home(2.0);
+  } else if (nm_total <= 230.0 * 256.0) {
+    rank_shapes(d, precision, [&](TileShape t, double homes, double stage) {
+      return tile_time(homes, stage, (double)tiles_of(d, t) * per_tile);
+    }, nmax, out);
+  } else if (by_home(3.0) > at_once && by_home(2.0) > at_once) {
+    by_home(3.0);
+  }
 }
 static void set_tile_shape(MeltDesc& d, TileShape t) {
   d.nl_S = t.S;

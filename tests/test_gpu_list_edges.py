@@ -100,6 +100,16 @@ def test_shapes_of_the_home_cost_fit_the_tile_map(melts, kw, shapes):
         assert b.nl_stats()["tile_shape"] == s
 
 
+@pytest.mark.parametrize("kw,tiles", [
+    (dict(nl_every=2), 880),           # 11 x 9 cells of 232 homes; three deviations in hand: 1,056, 24% slower
+    (dict(nl_every=5, T=2.0), 900),    # 6 x 5 of 222; two deviations in hand: 960, 11% slower
+    (dict(nl_every=5), 952),
+])
+def test_tiles_of_a_full_chip_run_at_once(kw, tiles):
+    m = kg.Melt(M=200, N=1000, kappa=2.0, warmup_steps=0, precision=1, **kw)
+    assert m.nl_stats()["tiles"] == tiles and tiles <= 4 * 256
+
+
 def test_step_time_of_long_lists():
     # 50,000 monomers at T = 2, whose lists hold 30 entries (a wider skin) instead of 19: 1.24 times the step
     # time of T = 1 (1.57 times when lists past the run were built a second time)
