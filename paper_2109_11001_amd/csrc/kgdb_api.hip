@@ -541,6 +541,14 @@ static int capture_chunk(kgdb_batch* b, int parity) {
   return 0;
 }
 
+// n / 2 when every melt has n = 2 or every one n = 12, else 0
+static int uniform_nh(const kgdb_batch* b) {
+  const int nh = b->D[0].n_half_int;
+  for (const MeltDesc& d : b->D)
+    if (d.n_half_int != nh) return 0;
+  return nh == 1 || nh == 6 ? nh : 0;
+}
+
 static NlArgs nl_args(kgdb_batch* b) {
   NlArgs a;
   std::memset(&a, 0, sizeof a);
@@ -551,10 +559,7 @@ static NlArgs nl_args(kgdb_batch* b) {
   a.rblk_melt = b->rm[b->nl_ki].melt;
   a.rblk_base = b->rm[b->nl_ki].base;
   a.stage_cap = b->stage_cap[b->nl_ki];
-  a.nh_uniform = b->D[0].n_half_int;
-  for (const MeltDesc& d : b->D)
-    if (d.n_half_int != a.nh_uniform) a.nh_uniform = 0;
-  if (a.nh_uniform != 1 && a.nh_uniform != 6) a.nh_uniform = 0;
+  a.nh_uniform = uniform_nh(b);
   a.NP = b->NP;
   a.ncl_total = 0;
   for (const MeltDesc& d : b->D) a.ncl_total += d.ncl * d.ncl * d.ncl;
@@ -952,9 +957,11 @@ static int stage_cap_for(const kgdb_batch* b, int q) {
     if (d.test_flags & TF_NL_GLOBAL) return 0;
   }
   const int cap = std::min(b->prec ? STAGE_CAP_MAX : STAGE_CAP_MAX_FP64, ((int)(1.5 * mx) + 64 + 63) / 64 * 64);
-  // FP64: four workgroups on a CU rather than three, while a quarter of the stage stays in hand (an
-  // equilibrated melt's stages vary by 2%; one that outgrows its capacity raises it for the next pass)
-  if (!b->prec && cap > STAGE_CAP_FP64_4 && 1.25 * mx + 64 <= STAGE_CAP_FP64_4) return STAGE_CAP_FP64_4;
+  // FP64 with n = 2 or 12 (the step of a general exponent has registers for two workgroups a CU): four
+  // workgroups on a CU rather than three, while a quarter of the stage stays in hand (an equilibrated
+  // melt's stages vary by 2%; one that outgrows its capacity raises it for the next pass)
+  if (!b->prec && uniform_nh(b) > 0 && cap > STAGE_CAP_FP64_4 && 1.25 * mx + 64 <= STAGE_CAP_FP64_4)
+    return STAGE_CAP_FP64_4;
   return cap;
 }
 
@@ -1449,6 +1456,8 @@ int kgdb_set_potential(kgdb_batch* b, int32_t melt, double n_exp, double k_fene)
   // work in flight (either stream) reads the melt table being replaced
   HIPCHK(hipStreamSynchronize(b->s));
   if (b->s2) HIPCHK(hipStreamSynchronize(b->s2));
+  int cap[3];
+  for (int q = 0; q < 3; ++q) cap[q] = stage_cap_for(b, q);
   for (int k = 0; k < b->nm; ++k) {
     if (melt >= 0 && k != melt) continue;
     b->P[k].n_exp = n_exp;
@@ -1456,6 +1465,8 @@ int kgdb_set_potential(kgdb_batch* b, int32_t melt, double n_exp, double k_fene)
     set_potential_desc(b->D[k], b->P[k]);
     for (auto& Dq : b->Dk) set_potential_desc(Dq[k], b->P[k]);
   }
+  for (int q = 0; q < 3; ++q)  // (a capacity that a pass has raised stays)
+    if (b->stage_cap[q] == cap[q]) b->stage_cap[q] = stage_cap_for(b, q);
   HIPCHK(hipMemcpyAsync(b->d_md, b->D.data(), sizeof(MeltDesc) * b->nm, hipMemcpyHostToDevice, b->s));
   // captured runs of steps hold the step kernel built for the old exponent
   for (auto& ge : b->gexec)

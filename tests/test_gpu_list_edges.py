@@ -110,6 +110,18 @@ def test_tiles_of_a_full_chip_run_at_once(kw, tiles):
     assert m.nl_stats()["tiles"] == tiles and tiles <= 4 * 256
 
 
+def test_stage_capacity_follows_the_exponent():
+    # FP64: the smaller stage that makes room for a fourth workgroup a CU is for the steps of n = 2 and 12; the
+    # step of a general exponent runs two and keeps the stage's full room
+    m = kg.Melt(M=200, N=1000, kappa=2.0, warmup_steps=0, precision=0, nl_every=5, n_exp=3.0)
+    wide = m.nl_stats()["stage_cap"]
+    seen = [wide]
+    for n in (2.0, 12.0, 5.75):
+        m.set_potential(n)
+        seen.append(m.nl_stats()["stage_cap"])
+    assert wide > 1472 and seen == [wide, 1472, 1472, wide]
+
+
 def test_step_time_of_long_lists():
     # 50,000 monomers at T = 2, whose lists hold 30 entries (a wider skin) instead of 19: 1.24 times the step
     # time of T = 1 (1.57 times when lists past the run were built a second time)
