@@ -225,3 +225,29 @@ def test_trained_network_raises_acceptance():
     print(f"acceptance uniform {rates[kg.PROPOSAL_UNIFORM]:.4f} learned {rates[kg.PROPOSAL_LEARNED]:.4f} "
           f"(loss {first:.4f} -> {last:.4f})", flush=True)
     assert rates[kg.PROPOSAL_LEARNED] > 1.5 * rates[kg.PROPOSAL_UNIFORM]
+
+
+@pytest.mark.parametrize("cap", [4096, 10, 1])
+def test_logged_sweep_of_lists_in_global_memory(cap):
+    # melts whose list is kept in global memory beside one whose list is in LDS, both logged, with room for
+    # every record and for a few
+    kws = [dict(M=20, N=50, seed=1, kappa=1.5), dict(M=30, N=40, seed=9, kappa=1.0), dict(M=25, N=31, seed=8, kappa=0.5)]
+    oms = [o.Melt(melt_id=k, **kw) for k, kw in enumerate(kws)]
+    b = kg.Batch([dict(kw, melt_id=k, warmup_steps=0, test_flags=kg.TF_DB_GLOBAL if k != 1 else 0)
+                  for k, kw in enumerate(kws)])
+    for k, om in enumerate(oms):
+        st = om.get_state()
+        b.set_state(k, x=st["x"], v=st["v"], fl=st["fl"], chains=st["chains"], counters=st["counters"])
+    accepted = 0
+    for sweep in range(2):
+        sg, fg, lg, nl = b.db_sweep_log(120, cap=cap)
+        for k, om in enumerate(oms):
+            so, fo, lo = om.db_sweep_log(120, cap=cap)
+            for f in STAT_FIELDS:
+                assert so[f] == sg[k][f], (k, f, so, sg[k])
+            assert nl[k] == len(lo) == min(cap, 120 - so["no_candidate"])
+            assert np.array_equal(fg[k, : nl[k]].cpu().numpy(), fo)
+            assert np.array_equal(lg[k, : nl[k]].cpu().numpy(), lo)
+            assert np.array_equal(om.get_state()["chains"], b.get_state(k)["chains"])
+            accepted += so["accepted"]
+    assert accepted > 0

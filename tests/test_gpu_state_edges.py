@@ -44,3 +44,22 @@ def test_state_in_id_order(M, N):
     F, S, _ = b.forces(1)
     Ft, St, _ = om.forces()
     assert np.all(np.abs(F - Ft) <= 1e-9 * np.maximum(St, 1.0)) and np.all(np.abs(S - St) <= 1e-9 * np.maximum(St, 1.0))
+
+
+@pytest.mark.parametrize("M,N", [(7, 31), (400, 111)])
+def test_some_arrays_of_a_state(M, N):
+    # any of a state's arrays may be left out: the others are those of the whole state, and nothing else of the
+    # caller's memory is written (44,400 monomers: chunks end inside arrays)
+    b = kg.Batch([dict(M=5, N=33, seed=9, warmup_steps=50), dict(M=M, N=N, seed=4, kappa=1.0, warmup_steps=50)])
+    b.md_steps(4)
+    full = b.get_state(1)
+    names = ("x", "v", "fc", "fl", "chains")
+    L = kg.load()
+    for take in (("x",), ("v", "chains"), ("fc",), ("fl", "x"), ("chains",), ("v", "fc", "fl"), ()):
+        guard = 64
+        bufs = {f: np.full(full[f].size + 2 * guard, -77, full[f].dtype) for f in take}
+        args = [kg.ptr(bufs[f][guard:]) if f in take else None for f in names]
+        kg.check(L.kgdb_get_state(b._h, 1, *args, None))
+        for f in take:
+            assert np.array_equal(bufs[f][guard:-guard], full[f].ravel()), (take, f)
+            assert np.all(bufs[f][:guard] == -77) and np.all(bufs[f][-guard:] == -77), (take, f)
