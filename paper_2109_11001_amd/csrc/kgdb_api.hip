@@ -6,7 +6,6 @@
 #include <cstdlib>
 #include <cstdio>
 #include <cstring>
-#include <functional>
 #include <initializer_list>
 #include <mutex>
 #include <string>
@@ -84,6 +83,7 @@ struct kgdb_batch {
   int* d_slot_of = nullptr;
   uint64_t* d_read = nullptr;
   uint64_t* h_read[2] = {nullptr, nullptr};
+  void* h_pin = nullptr;           // the handle's pinned memory (each h_ pointer lies in it)
   hipEvent_t ev_read[2] = {nullptr, nullptr};
   uint32_t read_words = 0;         // words of a chunk
   // neighbour lists (production steps)
@@ -274,11 +274,14 @@ static double tile_time(double homes, double stage, double tiles) {
 // tile): a workgroup stages 3 (nl_S + 2)(nl_Sy + 2) cells; the last tile of a row (column) takes the
 // remainder, and no tile is empty; the stage must fit the LDS cap with room for fluctuations.  out receives
 // up to nmax shapes, cheapest first.
-static void rank_shapes(const MeltDesc& d, int precision, const std::function<double(TileShape, double, double)>& cost,
-                        int nmax, std::vector<TileShape>& out) {
+template <typename Cost>
+static void rank_shapes(const MeltDesc& d, int precision, int nmax, std::vector<TileShape>& out, Cost cost) {
   const double occ = (double)d.Nm / ((double)d.ncl * d.ncl * d.ncl);
   const int cap = precision == KGDB_PREC_MIXED ? STAGE_CAP_MAX : STAGE_CAP_MAX_FP64;
-  std::vector<std::pair<double, TileShape>> all;
+  std::vector<double> best;
+  best.reserve(nmax + 1);
+  out.clear();
+  out.reserve(nmax + 1);
   for (int Sy = 1; Sy <= std::min(d.ncl, 64); ++Sy) {
     const int nyb = (d.ncl + Sy - 1) / Sy, Sye = (d.ncl + nyb - 1) / nyb;
     if (Sye != Sy) continue;
@@ -287,12 +290,14 @@ static void rank_shapes(const MeltDesc& d, int precision, const std::function<do
       if (Se != S || (S + 2) * (Sy + 2) > 198) continue;
       const double homes = S * Sy * occ, stage = 3.0 * (S + 2) * (Sy + 2) * occ;
       if (1.5 * stage + 64 > cap && !(S == 1 && Sy == 1)) continue;
-      all.push_back({cost(TileShape{S, Sy}, homes, stage), TileShape{S, Sy}});
+      const double c = cost(TileShape{S, Sy}, homes, stage);
+      if ((int)out.size() == nmax && c >= best.back()) continue;
+      const auto at = std::upper_bound(best.begin(), best.end(), c) - best.begin();  // (equal costs in order)
+      best.insert(best.begin() + at, c);
+      out.insert(out.begin() + at, TileShape{S, Sy});
+      if ((int)out.size() > nmax) { best.pop_back(); out.pop_back(); }
     }
   }
-  std::stable_sort(all.begin(), all.end(), [](const auto& x, const auto& y) { return x.first < y.first; });
-  out.clear();
-  for (size_t i = 0; i < all.size() && (int)out.size() < nmax; ++i) out.push_back(all[i].second);
   if (out.empty()) out.push_back(TileShape{1, 1});
 }
 static int64_t tiles_of(const MeltDesc& d, TileShape t) {
@@ -316,15 +321,15 @@ static double home_cost(double homes, double stage, double sd) {
 static void tile_shapes(const MeltDesc& d, int precision, double nm_total, int nmax, std::vector<TileShape>& out) {
   const double per_tile = nm_total / d.Nm, at_once = 4.0 * 256.0;
   auto by_home = [&](double sd) {
-    rank_shapes(d, precision, [sd](TileShape, double homes, double stage) { return home_cost(homes, stage, sd); }, nmax, out);
+    rank_shapes(d, precision, nmax, out, [sd](TileShape, double homes, double stage) { return home_cost(homes, stage, sd); });
     return (double)tiles_of(d, out[0]) * per_tile;
   };
   if (precision != KGDB_PREC_MIXED) {
     by_home(2.0);
   } else if (nm_total <= 230.0 * 256.0) {
-    rank_shapes(d, precision, [&](TileShape t, double homes, double stage) {
+    rank_shapes(d, precision, nmax, out, [&](TileShape t, double homes, double stage) {
       return tile_time(homes, stage, (double)tiles_of(d, t) * per_tile);
-    }, nmax, out);
+    });
   } else if (by_home(3.0) > at_once && by_home(2.0) > at_once) {
     by_home(3.0);
   }
@@ -347,10 +352,8 @@ static bool tile_shape_ok(const MeltDesc& d, int precision, TileShape t) {
   return 1.5 * 3.0 * (t.S + 2) * (t.Sy + 2) * occ + 64 <= cap;
 }
 
-// list grid of interval K in a batch of nm_total monomers, with the cheapest of its tile shapes; shapes
-// receives the nmax cheapest
-static void set_list_geometry(MeltDesc& d, const kgdb_params& p, int K, double nm_total, int nmax,
-                              std::vector<TileShape>& shapes) {
+// list grid of interval K in a batch of nm_total monomers (without its tiles)
+static void set_list_geometry(MeltDesc& d, const kgdb_params& p, int K, double nm_total) {
   const double rc = std::pow(2.0, 1.0 / 6.0);
   const double skin = nl_skin_for(p, K, nm_total);
   const double rl = rc + skin;
@@ -365,8 +368,7 @@ static void set_list_geometry(MeltDesc& d, const kgdb_params& p, int K, double n
   d.nl_wide = (double)d.Nm / ((double)d.ncl * d.ncl * d.ncl) > 6.5 ? 1 : 0;
   d.half_skin2 = 0.25 * skin * skin;
   d.half_skin = 0.5 * skin;
-  tile_shapes(d, p.precision, nm_total, nmax, shapes);
-  set_tile_shape(d, shapes[0]);
+  set_tile_shape(d, TileShape{1, 1});
 }
 
 static MeltDesc make_desc(const kgdb_params& p) {
@@ -396,8 +398,7 @@ static MeltDesc make_desc(const kgdb_params& p) {
   d.inv_mnb = 1.0 / ((double)d.M * (double)(d.N - 1));
   d.inv_nb = 1.0 / (double)(d.N - 1);
   d.lang_amp = std::sqrt(2.0 * p.gamma * p.T / p.dt);
-  std::vector<TileShape> sh;
-  set_list_geometry(d, p, p.nl_every > 0 ? p.nl_every : 5, (double)d.Nm, 1, sh);
+  set_list_geometry(d, p, p.nl_every > 0 ? p.nl_every : 5, (double)d.Nm);
   d.seed = p.seed;
   d.melt_id = (uint64_t)(int64_t)p.melt_id;
   d.init_mode = p.init_mode;
@@ -931,13 +932,9 @@ void kgdb_destroy(kgdb_batch* b) {
   if (b->ev_fork) hipEventDestroy(b->ev_fork);
   if (b->ev_join) hipEventDestroy(b->ev_join);
   for (auto e : b->ev_read) if (e) hipEventDestroy(e);
-  for (auto h : b->h_read) if (h) hipHostFree(h);
   if (b->s2) hipStreamDestroy(b->s2);
   for (void* q : b->allocs) hipFree(q);
-  if (b->h_err) hipHostFree(b->h_err);
-  if (b->h_nlstat) hipHostFree(b->h_nlstat);
-  if (b->h_stats) hipHostFree(b->h_stats);
-  if (b->h_err_side) hipHostFree(b->h_err_side);
+  if (b->h_pin) hipHostFree(b->h_pin);
   if (b->own_stream && b->s) hipStreamDestroy(b->s);
   delete b;
 }
@@ -1195,16 +1192,22 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
       // tiles of the batch when each melt takes its c-th candidate shape, and its c-th by the cost of a home
       // monomer with two deviations in hand
       std::vector<int64_t> tiles_c(2 * kgdb_batch::NSHAPE, 0);
+      std::vector<TileShape> by_home;
       for (int k = 0; k < count; ++k) {
         MeltDesc& d = b->Dk[q][k];
-        set_list_geometry(d, params[k], NL_KS[q], (double)NP, kgdb_batch::NSHAPE, b->shapes[q][k]);
+        set_list_geometry(d, params[k], NL_KS[q], (double)NP);
+        if (k > 0 && d.Nm == b->Dk[q][k - 1].Nm && d.ncl == b->Dk[q][k - 1].ncl) {  // as the melt before it
+          b->shapes[q][k] = b->shapes[q][k - 1];
+        } else {
+          tile_shapes(d, params[k].precision, (double)NP, kgdb_batch::NSHAPE, b->shapes[q][k]);
+          rank_shapes(d, params[k].precision, kgdb_batch::NSHAPE, by_home,
+                      [](TileShape, double homes, double stage) { return home_cost(homes, stage, 2.0); });
+        }
+        set_tile_shape(d, b->shapes[q][k][0]);
         d.celll_off = (int)off;
         d.tile_off = (int)toff;
         off += (int64_t)d.ncl * d.ncl * d.ncl;
         toff += (int64_t)d.ncl * d.nl_nyb * d.nl_nseg;
-        std::vector<TileShape> by_home;
-        rank_shapes(d, params[k].precision, [](TileShape, double homes, double stage) { return home_cost(homes, stage, 2.0); },
-                    kgdb_batch::NSHAPE, by_home);
         const std::vector<TileShape>* lists[2] = {&b->shapes[q][k], &by_home};
         for (int c = 0; c < 2 * kgdb_batch::NSHAPE; ++c) {
           const auto& v = *lists[c / kgdb_batch::NSHAPE];
@@ -1285,8 +1288,15 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
   step(dalloc(b, &b->d_nb4[1], np));
   step(dalloc(b, &b->d_inv, np));
   b->read_words = (uint32_t)std::min<size_t>(READ_WORDS, 12 * (size_t)b->max_Nm + (b->max_Nm + 1) / 2);
-  step(dalloc(b, &b->d_slot_of, np));
-  step(dalloc(b, &b->d_read, (size_t)b->read_words));
+  {
+    uint64_t* w = nullptr;
+    step(dalloc(b, &w, 4 * (size_t)neblk + b->read_words + (np + 1) / 2));
+    if (w) {
+      b->d_epart = (double4*)w;
+      b->d_read = w + 4 * neblk;
+      b->d_slot_of = (int*)(b->d_read + b->read_words);
+    }
+  }
   step(dalloc(b, &b->d_cntl, (size_t)b->NCL));
   step(dalloc(b, &b->d_tcnt, (size_t)b->NTILE));
   step(dalloc(b, &b->d_tstart, (size_t)b->NTILE));
@@ -1315,7 +1325,6 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
   step(dalloc(b, &b->d_step, (size_t)count));
   step(dalloc(b, &b->d_err, (size_t)count));
   step(dalloc(b, &b->d_out4, 4 * (size_t)count));
-  step(dalloc(b, &b->d_epart, (size_t)neblk));
   step(dalloc(b, &b->d_cnt13, (size_t)NC13));
   step(dalloc(b, &b->d_bucket13, (size_t)NC13 * DB_CELL_CAP));
   step(dalloc(b, &b->d_nnb, np));
@@ -1356,20 +1365,26 @@ static int init_impl(const kgdb_params* params, int32_t count, void* stream, kgd
   step(dalloc(b, &b->d_spre, 3 * (size_t)b->max_Nm));
   step(dalloc(b, &b->d_blen, (size_t)b->max_M));
   step(dalloc(b, &b->d_r2, (size_t)b->max_N));
-  if (!rc && hipHostMalloc((void**)&b->h_err, sizeof(uint32_t) * count, 0) != hipSuccess)
-    rc = fail(KGDB_E_ALLOC, "hipHostMalloc");
-  if (!rc && hipHostMalloc((void**)&b->h_nlstat, sizeof(uint32_t) * 2, 0) != hipSuccess)
-    rc = fail(KGDB_E_ALLOC, "hipHostMalloc");
-  if (!rc && hipHostMalloc((void**)&b->h_stats, sizeof(kgdb_db_stats) * count, 0) != hipSuccess)
-    rc = fail(KGDB_E_ALLOC, "hipHostMalloc");
-  if (!rc && hipHostMalloc((void**)&b->h_err_side, sizeof(uint32_t) * count, 0) != hipSuccess)
-    rc = fail(KGDB_E_ALLOC, "hipHostMalloc");
-  for (int q = 0; q < 2 && !rc; ++q) {
-    if (hipHostMalloc((void**)&b->h_read[q], sizeof(uint64_t) * b->read_words, 0) != hipSuccess)
-      rc = fail(KGDB_E_ALLOC, "hipHostMalloc");
-    else if (hipEventCreateWithFlags(&b->ev_read[q], hipEventDisableTiming) != hipSuccess)
-      rc = fail(KGDB_E_HIP, "hipEventCreate");
+  {
+    // one allocation: each takes 25-50 us here, and as long to be freed
+    char* base = nullptr;
+    size_t o = 0;
+    auto take = [&](size_t bytes) { char* q = base ? base + o : nullptr; o += (bytes + 255) & ~(size_t)255; return q; };
+    auto carve = [&] {
+      o = 0;
+      b->h_err = (uint32_t*)take(sizeof(uint32_t) * count);
+      b->h_nlstat = (uint32_t*)take(sizeof(uint32_t) * 2);
+      b->h_stats = (kgdb_db_stats*)take(sizeof(kgdb_db_stats) * count);
+      b->h_err_side = (uint32_t*)take(sizeof(uint32_t) * count);
+      for (auto& h : b->h_read) h = (uint64_t*)take(sizeof(uint64_t) * b->read_words);
+    };
+    carve();
+    if (!rc && hipHostMalloc(&b->h_pin, o, 0) != hipSuccess) rc = fail(KGDB_E_ALLOC, "hipHostMalloc");
+    base = (char*)b->h_pin;
+    carve();
   }
+  for (int q = 0; q < 2 && !rc; ++q)
+    if (hipEventCreateWithFlags(&b->ev_read[q], hipEventDisableTiming) != hipSuccess) rc = fail(KGDB_E_HIP, "hipEventCreate");
   if (!rc) rc = build_block_maps(b);
   if (rc) { kgdb_destroy(b); return rc; }
   if (const char* e = std::getenv("KGDB_FORCE_LANES")) {
