@@ -497,11 +497,6 @@ __device__ __forceinline__ int nl_list_one(const NlArgs& a, const ListArgs& l, i
   return cnt;
 }
 
-// One workgroup per tile, all resident at once at 200,000 monomers (952 tiles, 3.7 a CU: 128 registers and
-// a quarter of a CU's LDS each), so the launch lasts as long as its slowest tile.  Bound by latency: the
-// counts and members of the staged cells arrive in 5 + 6 us there (2.5 + 3 us on an idle chip), the
-// lists take 6-8 us.  1,000 monomers 18 us, 50,000 21 us, 200,000 39 us, 1M 126 us; with a thread per
-// cell, per-entry stores and FP32 positions gathered by slot 38, 41, 58 and 222 us.
 template <int CTRL>
 __device__ __forceinline__ int dpp(int v) {
   return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
@@ -524,6 +519,11 @@ __device__ __forceinline__ int group_rank(int v) {
   return r;
 }
 
+// One workgroup per tile, all resident at once at 200,000 monomers (952 tiles, 3.7 a CU: at most 128
+// registers, none in scratch, and a quarter of a CU's LDS each), so the launch lasts as long as its slowest
+// tile.  Bound by latency: the counts and members of the staged cells arrive in 5 + 6 us there (2.5 + 3 us on
+// an idle chip), the lists take 6-8 us.  1,000 monomers 18 us, 50,000 20 us, 200,000 38 us, 1M 124 us; with a
+// thread per cell, per-entry stores and FP32 positions gathered by slot 38, 41, 58 and 222 us.
 template <typename R>
 __global__ __launch_bounds__(NLB_THREADS, 4) void k_nl_rebuild(NlArgs a) {
   extern __shared__ __align__(16) unsigned char s_dyn[];
@@ -686,15 +686,7 @@ __global__ __launch_bounds__(NLB_THREADS, 4) void k_nl_rebuild(NlArgs a) {
       old = e.x;
       me = quant_pos(e, lx + 1, ly + 1, 1, U);
     }
-    // the new slot takes the monomer's state: its loads are issued here and stored after the
-    // list is built, so that they arrive while the list is built
     const int cx = wrapc(tg.x0 + lx, nc), cy = wrapc(tg.y0 + ly, nc), cz = tg.cz;
-    double xo[3], vo[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      xo[q] = a.x[(size_t)q * NP + old];
-      vo[q] = a.v[(size_t)q * NP + old];
-    }
     const int mo = a.mono[old];
     int n;
     if (staged)
@@ -705,6 +697,14 @@ __global__ __launch_bounds__(NLB_THREADS, 4) void k_nl_rebuild(NlArgs a) {
         const int row = q / W, i = q - row * W, zz = row / WY, yy = row - zz * WY;
         return quant_pos(member_entry(a, s_sc[q], s_off[q + 1] - s_off[q], u - s_off[q]), i, yy, zz, U);
       });
+    // the new slot takes the monomer's state (requested before the list was built, it arrived meanwhile, but
+    // its registers sent eight others to scratch: the same times up to 200,000 monomers, 2% more at 1M)
+    double xo[3], vo[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      xo[q] = a.x[(size_t)q * NP + old];
+      vo[q] = a.v[(size_t)q * NP + old];
+    }
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       a.xn[(size_t)q * NP + g] = xo[q];
