@@ -152,10 +152,11 @@ constexpr int TR_SG = NN_H + 2;  // row stride of the deltas: rows are 4 banks a
                                  // 16 rows by two columns touches every bank once
 static_assert(TR_WAVES * 32 == NN_H, "a wavefront owns 32 outputs of a layer");
 
-// the low or high bf16 of a register, without its sign
+// the low or high bf16 of a register (weights and inputs are signed)
 __device__ __forceinline__ double bf16_half(uint32_t v, int hi) {
   return (double)__uint_as_float(hi ? v & 0xffff0000u : v << 16);
 }
+// the same of two hidden codes, without the sign bit, which says that the unit passes gradient
 __device__ __forceinline__ double code_half(uint32_t v, int hi) {
   return (double)__uint_as_float(hi ? v & 0x7fff0000u : (v & 0x7fffu) << 16);
 }
