@@ -46,7 +46,6 @@ enum : uint32_t { TF_PHANTOM = 1u, TF_NOFORCE = 2u, TF_NL_GLOBAL = 4u, TF_SIDE_F
 // Per-melt constants, laid out for scalar loads (the melt index is uniform per workgroup).
 struct MeltDesc {
   int off, Nm, M, N;         // first global monomer, monomers, chains, beads per chain
-  int eblk_off;              // first block of 256 monomers (energy sums)
   int cell_off, nc;          // MD grid: first global cell, cells per side
   int cell13_off, nc13;      // double-bridging grid
   double L, cinv, h;         // box, nc / L, L / nc
@@ -85,6 +84,7 @@ struct MeltDesc {
   // constants of the step kernel: 1 / L, 1 / R0^2, and r_c^2 and 1 / u^2 in the units u of the
   // fixed-point relative positions (u = hl / 2^24)
   double invL, iR0sq, rc2_fx, iu2_fx;
+  int eblk_off;              // first block of 256 monomers (energy sums)
 };
 
 // ---------------------------------------------------------------------------------------
