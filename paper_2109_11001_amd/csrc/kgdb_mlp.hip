@@ -136,7 +136,8 @@ __global__ __launch_bounds__(256) void k_mlp_record(const NetQ* __restrict__ net
 // blocks of 16 x 16, 288 registers).  Nothing but the partial gradient leaves the workgroup.
 //
 // What bounds it: the FP64 products (139,264 flops a row: 102 us for 46,000 rows at the 62.8 TFLOP/s
-// a large FP64 matrix product reaches; measured 161 us, where the former per-thread loops took 1,650 us).
+// a large FP64 matrix product reaches; measured 162 us, the matrix cores busy for 53% of it, where the former
+// per-thread loops took 1,650 us); the rest is waits, for LDS and at the top of a row block for its record.
 // One wavefront per SIMD with 512 registers keeps the
 // gradient blocks, the weights and the next operands in registers; two of 256, with the forward
 // layers in the same kernel, had no room for operands ahead of their use and waited on LDS before

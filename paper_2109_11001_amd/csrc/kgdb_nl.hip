@@ -521,8 +521,8 @@ __device__ __forceinline__ int group_rank(int v) {
 
 // One workgroup per tile, all resident at once at 200,000 monomers (952 tiles, 3.7 a CU: at most 128
 // registers, none in scratch, and a quarter of a CU's LDS each), so the launch lasts as long as its slowest
-// tile.  Bound by latency: the counts and members of the staged cells arrive in 5 + 6 us there (2.5 + 3 us on
-// an idle chip), the lists take 6-8 us.  1,000 monomers 18 us, 50,000 20 us, 200,000 38 us, 1M 124 us; with a
+// tile.  Bound by latency (wavefronts wait 55% of their time, the VALU is busy 36%): the counts and members of
+// the staged cells arrive in 5 + 6 us there (2.5 + 3 us on an idle chip), the lists take 6-8 us.  1,000 monomers 18 us, 50,000 20 us, 200,000 38 us, 1M 124 us; with a
 // thread per cell, per-entry stores and FP32 positions gathered by slot 38, 41, 58 and 222 us.
 template <typename R>
 __global__ __launch_bounds__(NLB_THREADS, 4) void k_nl_rebuild(NlArgs a) {

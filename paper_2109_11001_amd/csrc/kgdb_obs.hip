@@ -265,8 +265,10 @@ __global__ __launch_bounds__(256) void k_r2(int M, int N, const double* __restri
 // (2 R + 1 <= nc), staged in LDS up to 1,536 at a time (the cells of a batch are cut where that is
 // reached): every thread holds two of these and runs over the home monomers.  Testing all pairs of a tile costs three times the distances that a
 // search cell by cell would need, but no gather, cell arithmetic or division per pair.  Bound by
-// VALU issue (the binning of a hit, which some lane of a wavefront nearly always has).  400,000
-// monomers to 3 sigma: 5.8 ms (a thread per monomer, gathers from L2) against 0.91 ms.
+// latency at two wavefronts a SIMD (62 KB of LDS a workgroup): half of their time they wait for LDS, the
+// coordinates and the bins' atomics (some lane of a wavefront nearly always has a hit), VALU issue takes
+// 46%.  400,000 monomers to 3 sigma: 5.8 ms (a thread per monomer, gathers from L2) against 0.9 ms; 4,000 at
+// density 1.2 0.78 against 0.24 (1.37 when a batch past the LDS was cut into pieces of 32 cells).
 constexpr int PH_B = 4;
 constexpr int PH_CELLS = 1024;  // cells per staged batch
 constexpr int PH_CAP = 1536;    // staged monomers
@@ -445,8 +447,9 @@ __global__ __launch_bounds__(256) void k_pair_hist(const MeltDesc* __restrict__ 
 // all lanes and come through scalar loads, so that a phasor costs arithmetic alone.  The phase is
 // taken in turns, w in [-1/2, 1/2] after rounding, and a quarter of it through the Taylor series of
 // sine and cosine (|pi w / 2| <= pi / 4: terms to the 16th power, the next below 5e-17), doubled
-// twice: 29 FP64 instructions.  Bound by their issue.  400,000 monomers x 5,600 vectors: 9.6 ms (a
-// workgroup per q with full-range sin and cos, 54 GB of coordinates read) against 2.2 ms.
+// twice: 29 FP64 instructions.  Bound by their issue (the VALU is busy 75% of the time).  400,000 monomers x
+// 5,600 vectors: 9.6 ms (a workgroup per q with full-range sin and cos, 54 GB of coordinates read) against
+// 2.2 ms.
 struct TurnSeries {
   double s[8], c[9];
 };
