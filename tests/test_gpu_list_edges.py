@@ -24,7 +24,6 @@ CASES = [
     dict(M=40, N=100, rho=1.3),   # rows of 24, lists of 29: some past 32
     dict(M=100, N=100, rho=0.85),  # five a cell (groups of 8, some cells past it)
     dict(M=37, N=61, rho=0.6),
-    dict(M=64, N=100, rho=1.5),   # rows and lists on both sides of 32, in the same wavefronts
 ]
 
 
@@ -50,6 +49,11 @@ def test_lists_at_the_edges(kw):
     assert np.array_equal(a["x"], b["x"]) and np.array_equal(a["v"], b["v"])
     assert melts["mixed"].nl_info()["K"] == 5
     assert melts["mixed"].nl_info()["mean_list"] == melts["global"].nl_info()["mean_list"]
+
+
+def test_lists_on_both_sides_of_the_run():
+    # rows and lists on both sides of 32, in the same wavefronts
+    test_lists_at_the_edges(dict(M=64, N=100, rho=1.5))
 
 
 @pytest.mark.parametrize("shape", [(5, 5), (5, 3), (3, 5)])
